@@ -502,6 +502,7 @@ struct DetectRun {
     int nrs = 0, nft = 0, nsc = 0, ncp = 0;  // tiles in use
     XcdLists xs{};     // FP32 scoring: the band table's per-XCD lists
     int s32_grid = 0;  // and its launch width
+    int s32_pairs = 0;  // FP32 scoring by the wave kernel: row pairs per wave (0: the band kernel)
     int32_t* s32_ctr = nullptr;
     float* s32_pack = nullptr;
     const NmsGeom* geoms = nullptr;
@@ -635,7 +636,11 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, const Tunin
         const std::vector<Tile> by_item(t_ft, t_ft + nft);
         for (const Tile& t : by_item) t_ft[start[rows_of(t)]++] = t;
     }
-    if (!L.bf16) nsc = score32_bands(items, q, tu.score_rows, tu.grid, t_sc, &R.xs, &R.s32_grid);
+    if (!L.bf16) {
+        R.s32_pairs = score32_wave_pairs((int64_t)L.n_sc * n_models);
+        nsc = R.s32_pairs ? score32_wave_tiles(items, q, t_sc)
+                          : score32_bands(items, q, tu.score_rows, tu.grid, t_sc, &R.xs, &R.s32_grid);
+    }
     const Tile* d_tiles = reinterpret_cast<const Tile*>(tbl + L.off_tiles);
     R.items = reinterpret_cast<const LevelItem*>(tbl + L.off_items);
     R.t_rs = d_tiles;
@@ -705,6 +710,16 @@ int enqueue_decide(const DetectRun& R, const DetectLayout& L, const float* weigh
                       "nms");
 }
 
+// FP32 scoring by the form fill_tables chose.
+hipError_t launch_score32(const DetectRun& R, const Tuning& tu, const float* weights, const float* bias, int n_models,
+                          int features, const Decide32& dec, hipStream_t s) {
+    if (R.s32_pairs)
+        return launch_score32_waves_table(R.items, R.t_sc, R.nsc, R.s32_pairs, weights, bias, n_models, features, dec,
+                                          s);
+    return launch_score32_table(R.items, R.t_sc, R.xs, R.s32_grid, R.s32_pack, bias, n_models, features,
+                                tu.score_rows, R.s32_ctr, dec, s);
+}
+
 // The kernel sequence of one call (tables already uploaded).  Only kernels are
 // enqueued here, so the sequence can be captured into a graph.
 int enqueue_detect(const DetectRun& R, const DetectLayout& L, const Tuning& tu, const float* weights,
@@ -713,7 +728,8 @@ int enqueue_detect(const DetectRun& R, const DetectLayout& L, const Tuning& tu, 
     int rc;
     marks.mark(PD_STAGE_ZERO, s);
     if ((rc = hip_status(launch_zero_i32(R.counters, R.n_zero, s), "zero"))) return rc;
-    if (!L.bf16 && (rc = hip_status(launch_pack_score32(weights, n_models, R.s32_pack, s), "pack"))) return rc;
+    if (!L.bf16 && !R.s32_pairs && (rc = hip_status(launch_pack_score32(weights, n_models, R.s32_pack, s), "pack")))
+        return rc;
     if (L.bf16) {
         if ((rc = hip_status(launch_orient_table(R.orient, s), "gradient table"))) return rc;
         if ((rc = hip_status(launch_pack_weights(weights, n_models, R.packed, s), "pack"))) return rc;
@@ -736,9 +752,7 @@ int enqueue_detect(const DetectRun& R, const DetectLayout& L, const Tuning& tu, 
         if (!L.bf16) {
             // FP32: bands span whole rows of 16-column tiles, which nearly
             // always hold a kept window; the keep set acts in compaction
-            rc = hip_status(launch_score32_table(R.items, R.t_sc, R.xs, R.s32_grid, R.s32_pack, bias, n_models,
-                                                 params->features, tu.score_rows, R.s32_ctr, Decide32{}, s),
-                            "score");
+            rc = hip_status(launch_score32(R, tu, weights, bias, n_models, params->features, Decide32{}, s), "score");
         } else if (L.rowgemm) {
             // one model: the row-GEMM kernel scores whole 64-column strips, which
             // nearly always hold a kept window; the keep set acts in compaction
@@ -779,12 +793,9 @@ int enqueue_detect(const DetectRun& R, const DetectLayout& L, const Tuning& tu, 
         // FP32 with one model: each window's score is final when stored, and
         // the scoring kernel appends the candidates itself (bands of 4 or 8
         // window rows per wave: the shapes with room for it)
-        decided = n_models == 1 && tu.score_rows != 16;
+        decided = n_models == 1 && (R.s32_pairs || tu.score_rows != 16);
         const Decide32 dec = decided ? Decide32{thresholds, R.counters, R.cscore, R.ckey} : Decide32{};
-        if ((rc = hip_status(launch_score32_table(R.items, R.t_sc, R.xs, R.s32_grid, R.s32_pack, bias, n_models,
-                                                  params->features, tu.score_rows, R.s32_ctr, dec, s),
-                             "score")))
-            return rc;
+        if ((rc = hip_status(launch_score32(R, tu, weights, bias, n_models, params->features, dec, s), "score"))) return rc;
     }
     marks.mark(PD_STAGE_COMPACT, s);
     return enqueue_decide(R, L, weights, bias, n_models, params, thresholds, n_frames, boxes, cap, counts, marks,
@@ -1115,9 +1126,7 @@ int pd_score_windows(const float* blocks, const uint8_t* cells, int cells_x, int
     it.hog = const_cast<float*>(blocks);
     it.lbp = const_cast<uint8_t*>(cells);
     it.scores = scores;
-    return hip_status(launch_score_single(it, weights, bias, n_models, PD_FEAT_HOG | PD_FEAT_LBP,
-                                          (hipStream_t)stream),
-                      "score launch");
+    return hip_status(launch_score_single(it, weights, bias, n_models, (hipStream_t)stream), "score launch");
 }
 
 int pd_lbp_naive(const uint8_t* codes, int w, int h, int codes_pitch, uint32_t* cell_hist, void* stream) {

@@ -88,10 +88,7 @@ constexpr int FT_W = 64;
 constexpr int FT_BX = 63;
 constexpr int FT_CH = 8;
 constexpr int FT_WAVES = 4;  // waves (independent strips) per workgroup
-// scoring: one wave = 64 window columns x SC_R window rows
-constexpr int SC_R = 8;
-constexpr int SC_W = 64;
-constexpr int SC_WAVES = 4;  // waves (independent tiles) per workgroup
+constexpr int SC_W = 64;  // window columns of a score tile
 // compaction: threads per workgroup, windows per thread, windows per workgroup
 constexpr int CP_THREADS = 256;
 constexpr int CP_PER = 4;
@@ -179,13 +176,11 @@ __host__ __device__ inline int feat_tiles_x(int wc) { return wc <= 1 ? 1 : ceil_
 constexpr int FT_BX_CM = 62;
 __host__ __device__ inline int feat_tiles_x_cm(int wc) { return ceil_div(wc, FT_BX_CM); }
 __host__ __device__ inline int feat_tiles_y(int hc, int rows = FT_CH) { return hc <= 1 ? 1 : ceil_div(hc - 1, rows); }
-__host__ __device__ inline int score_tiles_x(int nx) { return ceil_div(nx, SC_W); }
-__host__ __device__ inline int score_tiles_y(int ny, int rows = SC_R) { return ceil_div(ny, rows); }
 
 // Tile shapes and launch shapes chosen at run time (pd_params tuning fields).
 struct Tuning {
     int feat_rows = FT_CH;   // block rows per feature strip (2..32)
-    int score_rows = SC_R;   // FP32 scoring: window rows per band (4, 8 or 16)
+    int score_rows = 8;      // FP32 scoring: window rows per band (4, 8 or 16)
     int grid = 0;            // 0: one workgroup per tile group; > 0: at most this many, looping
 };
 
@@ -204,8 +199,8 @@ hipError_t launch_features_cellmap_single(const LevelItem& it, float clip, float
 hipError_t launch_features_cellmap_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip,
                                          float eps, const Tuning& tu, hipStream_t s);
 
-hipError_t launch_score_single(const LevelItem& it, const float* w, const float* bias, int n_models,
-                               int features, hipStream_t s);
+// FP32 scores of one image's windows (HOG and LBP), score32.hip.
+hipError_t launch_score_single(const LevelItem& it, const float* w, const float* bias, int n_models, hipStream_t s);
 // FP32 scoring on the matrix cores (score32.hip): bands of window rows over
 // runs of 16-column tiles, in 8 lists (one per XCD) taken through counters.
 struct XcdLists {
@@ -217,6 +212,11 @@ int64_t score32_packed_floats(int n_models);
 // the sum of score32_band_capacity over the items); returns its entry count.
 int score32_bands(const LevelItem* items, int n_items, int rows, int grid_cap, Tile* out, XcdLists* xs, int* grid);
 int64_t score32_band_capacity(int nx, int ny, int wc);
+// The form for few windows (same bits): its table, the row pairs per wave that
+// suit n_entries of it (0: too many, the band kernel), and its launch on the
+// caller's own weights.
+int score32_wave_tiles(const LevelItem* items, int n_items, Tile* out);
+int score32_wave_pairs(int64_t n_entries);
 hipError_t launch_pack_score32(const float* w, int n_models, float* out, hipStream_t s);
 // Threshold decisions taken as the FP32 scores are stored (one model, no
 // keep set): windows above their frame's threshold are appended to the
@@ -231,6 +231,10 @@ struct Decide32 {
 hipError_t launch_score32_table(const LevelItem* items, const Tile* bands, const XcdLists& xs, int grid,
                                 const float* packed, const float* bias, int n_models, int features, int rows,
                                 int* ctr, const Decide32& dec, hipStream_t s);
+
+hipError_t launch_score32_waves_table(const LevelItem* items, const Tile* tiles, int n_tiles, int pairs,
+                                      const float* weights, const float* bias, int n_models, int features,
+                                      const Decide32& dec, hipStream_t s);
 
 // Error reporting of the C ABI: sets the calling thread's message and
 // returns `code` (fail) or maps a HIP status (hip_status: PD_OK or PD_E_HIP).

@@ -48,6 +48,7 @@
 // bias.
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 #include <vector>
 
 #include "pd_internal.h"
@@ -406,6 +407,333 @@ score32_kernel(const LevelItem* __restrict__ items, const Tile* __restrict__ ban
     }
 }
 
+// ---- few windows: a wave per sub-tile and NQ row pairs ---------------------
+// The band kernel above walks 47 feature rows per tile in turn, two tiles and
+// a lead per run, so one 1242x375 pyramid took 281 us on 26 workgroups, and a
+// single image in the vector-ALU form that preceded this one 327 us on 3.  Here
+// every (sub-tile, NQ row pairs) is a wave of its own: the longest serial chain
+// is the one the order of a window's sum asks for (2 NQ + 15 feature rows of 24
+// dependent MFMAs, 6.6 us at NQ = 1).  The pyramid takes 31 us, a level 20 us;
+// what bounds it now is the rows' lines from L2 (each of a wave's 95 planes
+// gives a row 16 or 64 bytes of a 128-byte line; prefetching deeper, fewer waves
+// per workgroup and pipelining the LDS pass measured no gain).  What a wave
+// computes, and in which order, is the band kernel's: the same bits.
+//
+// A table entry (or, for one image, a block index) is a band of SW_PAIRS row
+// pairs x 2 tiles; block y picks NQ of its pairs, and the workgroup's waves are
+// the lead sub-tile (left of the entry, only its carry is wanted) and the 8
+// sub-tiles of the two tiles.  The model is packed into LDS straight from the
+// caller's weights, so no packing launch precedes this one.
+constexpr int SW_PAIRS = 8;             // row pairs per table entry
+constexpr int SW_RUN = 2;               // tiles per table entry
+constexpr int SW_SUBS = SW_RUN * S32_SUBS;
+constexpr int SW_THREADS = 64 * (SW_SUBS + 1);  // a wave per sub-tile, and one for the lead sub-tile
+constexpr int SW_WG_HOG = PD_HOG_DIM / 4;  // 16-byte pieces of a model's weights
+constexpr int SW_WG = PD_FEATURE_DIM / 4;
+static_assert(PD_HOG_BLOCK % 4 == 0 && PD_FEATURE_DIM % 4 == 0 && PD_WIN_CELLS_Y * PD_WIN_CELLS_X <= 320, "model pieces");
+
+//
+// CHECK (features the caller made): a non-finite HOG value would reach windows
+// that do not hold it through the zero weights around the model, so a
+// workgroup that met one sums its windows term by term instead.
+__device__ __forceinline__ float plain_score(const LevelItem& it, const float* __restrict__ w, float bias, int i, int j) {
+    const size_t hplane = (size_t)(it.hc - 1) * (it.wc - 1), lplane = (size_t)it.hc * it.wc;
+    float sum = 0.0f;
+#pragma unroll 1
+    for (int a = 0; a < PD_WIN_BLOCKS_Y; ++a)
+#pragma unroll 1
+        for (int b = 0; b < PD_WIN_BLOCKS_X; ++b)
+#pragma unroll 1
+            for (int c = 0; c < PD_HOG_BLOCK; ++c)
+                sum = fmaf(it.hog[c * hplane + (size_t)(i + a) * (it.wc - 1) + j + b], *w++, sum);
+#pragma unroll 1
+    for (int a = 0; a < PD_WIN_CELLS_Y; ++a)
+#pragma unroll 1
+        for (int b = 0; b < PD_WIN_CELLS_X; ++b)
+#pragma unroll 1
+            for (int c = 0; c < PD_LBP_BINS; ++c)
+                sum = fmaf((float)it.lbp[c * lplane + (size_t)(i + a) * it.wc + j + b], *w++, sum);
+    return sum + bias;
+}
+
+template <int FEAT, int NQ, bool CHECK = false>
+__device__ __forceinline__ void score32_waves(const LevelItem& it, int i0, int tx, int n_tiles, int group,
+                                              const float* __restrict__ weights, const float* __restrict__ bias,
+                                              int model, const Decide32& dec) {
+    constexpr bool HOG = (FEAT & PD_FEAT_HOG) != 0, LBP = (FEAT & PD_FEAT_LBP) != 0;
+    constexpr int K = LBP ? S32_LBP_K : S32_HOG_K;
+    constexpr int O_FLOATS = 16 * S32_OS, C_FLOATS = NQ * 16;
+    constexpr int DEPTH = 2;  // feature rows in flight
+    constexpr int NT = SW_THREADS;
+    static_assert((O_FLOATS + C_FLOATS) * 4 <= S32_STAGE && NQ * 32 <= O_FLOATS, "write-back scratch");
+    __shared__ __attribute__((aligned(16))) float wsh[S32_MODEL];
+    __shared__ __attribute__((aligned(16))) uint8_t stg[SW_SUBS + 1][S32_STAGE];
+    __shared__ int odd[SW_SUBS + 1];  // CHECK: the wave met a non-finite value
+    const int wc = it.wc, hc = it.hc, wb = wc - 1, hb = hc - 1, nx = it.nx, ny = it.ny;
+    i0 += 2 * NQ * group;
+    const int np = min(NQ, (ny - i0 + 1) >> 1);
+    if (np <= 0) return;  // the whole workgroup: the level ends above these pairs
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sub = S32_SUBS * tx + wave - 1;  // this wave's sub-tile of the level's row
+    const int n_sub = min((wc + S32_SUB - 1) / S32_SUB, S32_SUBS * (tx + n_tiles));
+    const bool busy = sub >= 0 && sub < n_sub;  // uniform per wave
+    const int j0 = S32_SUB * sub;
+    uint8_t* const st = stg[wave];
+    auto is_h = [&](int q) { return HOG && lane + 64 * q < S32_PIECES_H; };
+    auto is_l = [&](int q) { return LBP && lane + 64 * q >= S32_PIECES_H && lane + 64 * q < S32_PIECES; };
+    const uint32_t hplane = (uint32_t)hb * (uint32_t)wb, lplane = (uint32_t)hc * (uint32_t)wc;
+    const auto rh = planes_rsrc(it.hog, (uint64_t)PD_HOG_BLOCK * hplane * 4);
+    const auto rl = planes_rsrc(it.lbp, (uint64_t)PD_LBP_BINS * lplane);
+    struct RowRegs {
+        u32x4 v[S32_PPT];
+    };
+    uint32_t voff[S32_PPT];
+#pragma unroll
+    for (int q = 0; q < S32_PPT; ++q) {
+        const int e = lane + 64 * q;
+        voff[q] = is_h(q) ? ((uint32_t)(e >> 2) * hplane + (uint32_t)(j0 + 4 * (e & 3))) * 4u
+                          : (uint32_t)max(e - S32_PIECES_H, 0) * lplane + (uint32_t)j0;
+    }
+    auto load = [&](int r, RowRegs& g) __attribute__((always_inline)) {
+        const uint32_t roh = (uint32_t)min(i0 + r, hb - 1) * (uint32_t)wb * 4u;
+        const uint32_t rol = (uint32_t)min(i0 + r, hc - 1) * (uint32_t)wc;
+#pragma unroll
+        for (int q = 0; q < S32_PPT; ++q) {
+            if (is_h(q))
+                g.v[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rh, voff[q], roh, 0));
+            else if (is_l(q))
+                g.v[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rl, voff[q], rol, 0));
+        }
+    };
+    // A piece of the last cell row that reaches past the level's columns can
+    // start inside the planes' last word and run past their end: the buffer
+    // drops that whole word, so the row's LBP bytes are staged one by one.
+    auto stage_last = [&]() __attribute__((always_inline)) {
+        for (int e = lane; e < PD_LBP_BINS * S32_SUB; e += 64)
+            st[S32_STG_LBP + e] = __builtin_amdgcn_raw_buffer_load_b8(
+                rl, (uint32_t)(e / S32_SUB) * lplane + (uint32_t)(j0 + e % S32_SUB), (uint32_t)(hc - 1) * (uint32_t)wc, 0);
+    };
+    // the first rows' loads are in flight while the model is packed
+    RowRegs g[DEPTH];
+    if (busy) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) load(d, g[d]);
+    }
+    {
+        // the model as it lies in memory, 16 bytes per load (every load of a
+        // thread in flight together; a load past the end repeats the last one)
+        const float* wm = weights + (size_t)model * PD_FEATURE_DIM;
+        constexpr int PER = (SW_WG + NT - 1) / NT;
+        float4 w4[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) __builtin_memcpy(&w4[k], wm + 4 * min(tid + NT * k, SW_WG - 1), 16);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int e = min(tid + NT * k, SW_WG - 1);
+            if (e < SW_WG_HOG) {  // one (a, b) and chunk
+                const int ab = e / S32_HOG_T, t = e - ab * S32_HOG_T;
+                const int a = ab / PD_WIN_BLOCKS_X, b = ab - a * PD_WIN_BLOCKS_X;
+                float* o = wsh + a * S32_HOG_RS + 32 * t + 4 * b;
+                *reinterpret_cast<float2*>(o) = make_float2(w4[k].x, w4[k].y);
+                *reinterpret_cast<float2*>(o + 2) = make_float2(w4[k].z, w4[k].w);
+            } else {
+                const float v[4] = {w4[k].x, w4[k].y, w4[k].z, w4[k].w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int f = 4 * (e - SW_WG_HOG) + i, ab = f / PD_LBP_BINS, c = f - ab * PD_LBP_BINS;
+                    wsh[S32_HOG_N + (ab >> 3) * S32_LBP_RS + 32 * (c >> 2) + 4 * (ab & 7) + (c & 3)] = v[i];
+                }
+            }
+        }
+        // LBP channel 59
+        if (tid < PD_WIN_CELLS_Y * PD_WIN_CELLS_X)
+            wsh[S32_HOG_N + (tid >> 3) * S32_LBP_RS + 32 * (S32_LBP_T - 1) + 4 * (tid & 7) + 3] = 0.0f;
+        // HOG's eighth column offset and the row outside the model
+        for (int e = tid; e < PD_WIN_BLOCKS_Y * S32_HOG_T * 4; e += NT) {
+            const int a = e / (S32_HOG_T * 4), x = e - a * (S32_HOG_T * 4);
+            wsh[a * S32_HOG_RS + 32 * (x >> 2) + 4 * PD_WIN_BLOCKS_X + (x & 3)] = 0.0f;
+        }
+        for (int e = tid; e < S32_MODEL - S32_ZERO; e += NT) wsh[S32_ZERO + e] = 0.0f;
+    }
+    __syncthreads();
+
+    const int col = lane & 15, kk = lane >> 4;    // A: feature column, channel within the chunk
+    const int s = (lane >> 3) & 1, b = lane & 7;  // B: window row in the pair, column offset
+    const int blane = 4 * b + kk;
+    float* const ow = reinterpret_cast<float*>(st);
+    const int e_s = (lane >> 4) & 1, e_w = lane & 15;
+    const float* const oe = ow + 8 * e_s;
+    float part[NQ], chk = 0.0f;  // chk stays 0 where the wave has no sub-tile
+    if (busy) {
+        // CHECK (its scores need not be the band kernel's bits): several chains
+        // per pair, HOG and LBP, with one pair the even and odd LBP chunks too,
+        // summed at the end: shorter sums (error against 64 bits 2.5e-7 of the
+        // scores' norm, 4e-7 in one chain), and MFMAs that do not wait for each
+        // other
+        constexpr int NC = !CHECK ? 1 : NQ == 1 ? 3 : 2;
+        f32x4 acc[NQ][NC];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[q][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        const int nrows = 2 * np + K - 2;
+        struct Frags {  // a row's A fragments: HOG values, LBP counts
+            float h[S32_HOG_T];
+            uint8_t l[S32_LBP_T];
+        };
+        // row r through the wave's LDS (its operations run in order) into A
+        // fragments; the loads of row r + DEPTH take its registers
+        auto stage = [&](int r, RowRegs& g, Frags& f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < S32_PPT; ++q)
+                if (is_h(q) || is_l(q)) *reinterpret_cast<u32x4*>(st + 16 * (lane + 64 * q)) = g.v[q];
+            load(r + DEPTH, g);
+            if (LBP && i0 + r >= hc - 1 && j0 + S32_SUB > wc) stage_last();  // uniform
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int t = 0; t < S32_HOG_T; ++t)
+                if (HOG) f.h[t] = reinterpret_cast<const float*>(st)[64 * t + lane];
+#pragma unroll
+            for (int t = 0; t < S32_LBP_T; ++t)
+                if (LBP) f.l[t] = st[S32_STG_LBP + 64 * t + lane];
+            __builtin_amdgcn_wave_barrier();
+        };
+        auto multiply = [&](int r, const Frags& f) __attribute__((always_inline)) {
+            if constexpr (CHECK && HOG) {
+#pragma unroll
+                for (int t = 0; t < S32_HOG_T; ++t) chk = fmaf(f.h[t], 0.0f, chk);  // NaN from the first inf or NaN on
+            }
+            float lf[S32_LBP_T];
+#pragma unroll
+            for (int t = 0; t < S32_LBP_T; ++t) lf[t] = LBP ? (float)f.l[t] : 0.0f;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int a = r - 2 * q;  // K row of pair q (uniform)
+                if (q >= np || a < 0 || a >= K) continue;
+                const int w = a - s;
+                if constexpr (HOG) {
+                    if (a < S32_HOG_K) {
+                        const float* bp =
+                            wsh + ((unsigned)w < (unsigned)PD_WIN_BLOCKS_Y ? w * S32_HOG_RS : S32_ZERO) + blane;
+#pragma unroll
+                        for (int t = 0; t < S32_HOG_T; ++t)
+                            acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.h[t], bp[32 * t], acc[q][0], 0, 0, 0);
+                    }
+                }
+                if constexpr (LBP) {
+                    const float* bp =
+                        wsh + ((unsigned)w < (unsigned)PD_WIN_CELLS_Y ? S32_HOG_N + w * S32_LBP_RS : S32_ZERO) + blane;
+#pragma unroll
+                    for (int t = 0; t < S32_LBP_T; ++t) {
+                        f32x4& sum = acc[q][NC == 1 ? 0 : NC == 2 ? 1 : 1 + (t & 1)];
+                        sum = __builtin_amdgcn_mfma_f32_16x16x4f32(lf[t], bp[32 * t], sum, 0, 0, 0);
+                    }
+                }
+            }
+        };
+        for (int r0 = 0; r0 < nrows; r0 += DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                if (r0 + d >= nrows) break;  // uniform
+                Frags f;
+                stage(r0 + d, g[d], f);
+                multiply(r0 + d, f);
+            }
+        }
+        // the diagonals: this sub-tile's part of each window and the carry for
+        // the next one, as the band kernel sums them
+        float* const cw = ow + O_FLOATS;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            part[q] = 0.0f;
+            if (q >= np) continue;  // uniform
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                ow[(4 * kk + v) * S32_OS + col] =
+                    NC == 1   ? acc[q][0][v]
+                    : NC == 2 ? acc[q][0][v] + acc[q][NC - 1][v]
+                              : acc[q][0][v] + (acc[q][NC - 2][v] + acc[q][NC - 1][v]);
+            __builtin_amdgcn_wave_barrier();
+            if (lane < 32) {
+                float sum = 0.0f;
+#pragma unroll
+                for (int bb = 0; bb < 8; ++bb) {
+                    const int m = e_w - 7 + bb;
+                    sum += m >= 0 ? oe[max(m, 0) * S32_OS + bb] : 0.0f;
+                }
+                float next = 0.0f;
+#pragma unroll
+                for (int bb = 0; bb < 7; ++bb) {
+                    const int m = 9 + e_w + bb;
+                    next += m < 16 ? oe[min(m, 15) * S32_OS + bb] : 0.0f;
+                }
+                part[q] = sum;
+                if (e_w < 8) cw[q * 16 + e_s * 8 + e_w] = next;
+            }
+        }
+    }
+    if constexpr (CHECK) {
+        const bool any = __any(chk != 0.0f);  // NaN is not 0
+        if (lane == 0) odd[wave] = any;
+    }
+    __syncthreads();
+    if (!busy || wave == 0 || lane >= 32) return;
+    const float* cin = sub > 0 ? reinterpret_cast<const float*>(stg[wave - 1]) + O_FLOATS : nullptr;
+    const int jw = j0 - 7 + e_w;
+    const float bm = bias[model];
+    const auto out = gmem(it.scores) + (size_t)model * ny * nx;
+    int32_t* const count = dec.counters ? dec.counters + it.frame : nullptr;
+    const double thr = count ? dec.thr[it.frame] : 0.0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if (q >= np) break;  // uniform
+        const float c = cin && e_w < 8 ? cin[q * 16 + e_s * 8 + e_w] : 0.0f;
+        const int i = i0 + 2 * q + e_s;
+        const bool in = jw >= 0 && jw < nx && i < ny;
+        float v = (part[q] + c) + bm;
+        if constexpr (CHECK) {
+            if ((odd[wave] | odd[wave - 1]) && in) v = plain_score(it, weights + (size_t)model * PD_FEATURE_DIM, bm, i, jw);
+        }
+        if (in) out[(size_t)i * nx + jw] = v;
+        if (!count) continue;
+        // the decision (Section 4.4): one atomic per wave and pair
+        const bool cand = in && (double)v > thr;
+        const uint64_t m = __ballot(cand);
+        if (!m) continue;
+        const int first_lane = __builtin_ctzll(m);
+        int base = 0;
+        if (lane == first_lane) base = atomicAdd(count, __popcll(m));
+        base = __shfl(base, first_lane, 64);
+        if (cand) {
+            const int pos = base + __popcll(m & ((1ull << lane) - 1ull));
+            if (pos < it.cand_cap) {  // always: a window is appended once at most
+                dec.cscore[it.cand_off + pos] = v;
+                dec.ckey[it.cand_off + pos] = make_int4(it.level, i, jw, 0);
+            }
+        }
+    }
+}
+
+template <int FEAT, int NQ>
+__global__ void __launch_bounds__(SW_THREADS) __attribute__((amdgpu_waves_per_eu(5)))
+score32_waves_table_kernel(const LevelItem* __restrict__ items, const Tile* __restrict__ tiles,
+                           const float* __restrict__ weights, const float* __restrict__ bias, Decide32 dec) {
+    const Tile t = tiles[blockIdx.x];
+    score32_waves<FEAT, NQ>(items[t.item], t.ty, t.tx, t.pad, blockIdx.y, weights, bias, blockIdx.z, dec);
+}
+
+// One image: block x = (band, run of SW_RUN tiles).
+template <int NQ>
+__global__ void __launch_bounds__(SW_THREADS) __attribute__((amdgpu_waves_per_eu(5)))
+score32_waves_single_kernel(LevelItem it, const float* __restrict__ weights, const float* __restrict__ bias) {
+    const int runs = (it.wc + SW_RUN * S32_TILE - 1) / (SW_RUN * S32_TILE);
+    const int band = blockIdx.x / runs, run = blockIdx.x - band * runs;
+    score32_waves<PD_FEAT_HOG | PD_FEAT_LBP, NQ, true>(it, band * 2 * SW_PAIRS, run * SW_RUN, SW_RUN, blockIdx.y,
+                                                             weights, bias, blockIdx.z, Decide32{});
+}
+
 // row pairs per band for the tuning field's window rows per wave (4, 8, 16)
 constexpr int s32_pairs(int rows) { return rows == 4 ? 8 : rows == 16 ? 24 : 16; }
 
@@ -506,6 +834,29 @@ int score32_bands(const LevelItem* items, int n_items, int rows, int grid_cap, T
     return n;
 }
 
+// The wave kernel's table: bands of SW_PAIRS row pairs over runs of SW_RUN
+// tiles (the table capacity below counts exactly these), largest levels first
+// as the items come.
+int score32_wave_tiles(const LevelItem* items, int n_items, Tile* out) {
+    int n = 0;
+    for (int q = 0; q < n_items; ++q) {
+        if (items[q].nx <= 0 || items[q].ny <= 0) continue;
+        const int nt = ceil_div(items[q].wc, S32_TILE);
+        for (int i0 = 0; i0 < items[q].ny; i0 += 2 * SW_PAIRS)
+            for (int tx = 0; tx < nt; tx += SW_RUN) out[n++] = Tile{q, i0, tx, std::min(SW_RUN, nt - tx)};
+    }
+    return n;
+}
+
+// Row pairs per wave for a launch of n_entries bands.  One pair while every
+// workgroup then has a CU of its own (one 1242x375 pyramid: 30 us, 44 with two
+// pairs), two up to about 32 such frames (4: 72 us, the band kernel 283; 16: 182
+// and 287; 32: 337 and 352), above that the band kernel (64: 680 and 550; 0).
+int score32_wave_pairs(int64_t n_entries) {
+    if (n_entries * SW_PAIRS <= 256) return 1;
+    return n_entries <= 700 ? 2 : 0;
+}
+
 // Table capacity for one level: the shortest bands over runs of 2 tiles, the
 // finest the builder makes.
 int64_t score32_band_capacity(int nx, int ny, int wc) {
@@ -532,6 +883,36 @@ hipError_t launch_score32_table(const LevelItem* items, const Tile* bands, const
         case PD_FEAT_LBP: launch_feat<PD_FEAT_LBP>(rows, g, items, bands, xs, packed, bias, ctr, dec, s); break;
         default: launch_feat<PD_FEAT_HOG | PD_FEAT_LBP>(rows, g, items, bands, xs, packed, bias, ctr, dec, s); break;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_score32_waves_table(const LevelItem* items, const Tile* tiles, int n_tiles, int pairs,
+                                      const float* weights, const float* bias, int n_models, int features,
+                                      const Decide32& dec, hipStream_t s) {
+    if (n_tiles <= 0 || n_models <= 0) return hipSuccess;
+    if (dec.counters && n_models != 1) return hipErrorInvalidValue;  // decisions need the max over the models
+    const dim3 g((unsigned)n_tiles, (unsigned)(SW_PAIRS / pairs), (unsigned)n_models);
+    auto run = [&](auto feat) {
+        constexpr int F = decltype(feat)::value;
+        if (pairs == 1) score32_waves_table_kernel<F, 1><<<g, SW_THREADS, 0, s>>>(items, tiles, weights, bias, dec);
+        else score32_waves_table_kernel<F, 2><<<g, SW_THREADS, 0, s>>>(items, tiles, weights, bias, dec);
+    };
+    switch (features & (PD_FEAT_HOG | PD_FEAT_LBP)) {
+        case PD_FEAT_HOG: run(std::integral_constant<int, PD_FEAT_HOG>{}); break;
+        case PD_FEAT_LBP: run(std::integral_constant<int, PD_FEAT_LBP>{}); break;
+        default: run(std::integral_constant<int, PD_FEAT_HOG | PD_FEAT_LBP>{}); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_score_single(const LevelItem& it, const float* weights, const float* bias, int n_models,
+                               hipStream_t s) {
+    if (it.nx <= 0 || it.ny <= 0 || n_models <= 0) return hipSuccess;
+    const int n = ceil_div(it.ny, 2 * SW_PAIRS) * ceil_div(it.wc, SW_RUN * S32_TILE);
+    const int pairs = score32_wave_pairs((int64_t)n * n_models) == 1 ? 1 : 2;
+    const dim3 g((unsigned)n, (unsigned)(SW_PAIRS / pairs), (unsigned)n_models);
+    if (pairs == 1) score32_waves_single_kernel<1><<<g, SW_THREADS, 0, s>>>(it, weights, bias);
+    else score32_waves_single_kernel<2><<<g, SW_THREADS, 0, s>>>(it, weights, bias);
     return hipGetLastError();
 }
 
