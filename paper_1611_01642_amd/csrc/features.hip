@@ -27,6 +27,8 @@
 // (coalesced).  Strips overlap by one cell column, chunks by one cell row.
 //
 // Sums run in a fixed order, so results are bitwise reproducible.
+#include <algorithm>
+
 #include "pd_internal.h"
 
 namespace pd {
@@ -84,18 +86,16 @@ struct PixRow {
     uint32_t r0, r1;   // bytes 2..5 and 6..9: the right neighbours of lo, hi
 };
 
-template <bool ALIGNED>
+// A row's pixels need not be 8-byte aligned (global loads of any alignment are
+// one instruction on this machine).
+typedef uint64_t __attribute__((aligned(1))) u64_any;
+
 __device__ __forceinline__ PixRow load_row(gptr<const uint8_t> __restrict__ img, int pitch, int w, int y, int x0) {
     const auto p = img + (size_t)y * pitch + x0;
     PixRow r;
-    if (ALIGNED) {
-        const uint64_t m = *reinterpret_cast<gptr<const uint64_t>>(p);
-        r.lo = (uint32_t)m;
-        r.hi = (uint32_t)(m >> 32);
-    } else {
-        r.lo = (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16) | ((uint32_t)p[3] << 24);
-        r.hi = (uint32_t)p[4] | ((uint32_t)p[5] << 8) | ((uint32_t)p[6] << 16) | ((uint32_t)p[7] << 24);
-    }
+    const uint64_t m = *reinterpret_cast<gptr<const u64_any>>(p);
+    r.lo = (uint32_t)m;
+    r.hi = (uint32_t)(m >> 32);
     // the halo bytes (clamped at the image edges) from their own addresses, so
     // that no value depends on another load before it is used
     const auto row = img + (size_t)y * pitch;
@@ -138,52 +138,54 @@ __device__ __forceinline__ int px_at(const PixRow& r, int i) {  // i in 0..9, co
     return (int)(((b < 4 ? r.lo : r.hi) >> (8 * (b & 3))) & 255u);
 }
 
-// With CM the strip also emits the pruner's cell map: per cell, the 9-bin
-// histogram with the full bilinear spatial kernel (every vote aimed at the
-// cell: its own pixels' and its 8 neighbours', Sum_d A[c - d][d]), divided by
-// sqrt(|h|^2 + eps^2), then the 59 LBP counts / 64: FP32 planar
-// [68][hc][wc] (cmap) and/or BF16 channels-last [hc][wc][72] (cmap16).
-// Lanes 1..62 own columns tx*62 .. tx*62 + 61, lanes 0 and 63 are halo, and
-// the strip starts half a cell row early (the downward votes of the row
-// above), so each owned cell sees all of its neighbours' partials.
-template <int FEAT, bool ALIGNED, bool CM = false>
-__device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ img, int w, int h, int pitch,
-                                               gptr<float> __restrict__ hog, gptr<uint16_t> __restrict__ hog16,
-                                               gptr<uint8_t> __restrict__ lbp, gptr<float> __restrict__ cmap,
-                                               gptr<uint16_t> __restrict__ cmap16, int ty, int tx, int ch, float clip,
-                                               float eps, FeatShared& sm, int wave, int group = 64) {
-    constexpr bool DO_HOG = (FEAT & PD_FEAT_HOG) != 0;
-    constexpr bool DO_LBP = (FEAT & PD_FEAT_LBP) != 0;
+// One lane's cell column: where its pixels, accumulators and outputs are, and
+// the steps the strip and the row kernels share.
+template <int FEAT, bool CM>
+struct Lane {
+    static constexpr bool DO_HOG = (FEAT & PD_FEAT_HOG) != 0;
+    static constexpr bool DO_LBP = (FEAT & PD_FEAT_LBP) != 0;
     static_assert(!CM || (DO_HOG && DO_LBP), "the cell map needs HOG and LBP");
-    const int lane = threadIdx.x & 63;
-    const int hc = h / PD_CELL, wc = w / PD_CELL;
-    const int hb = hc - 1, wb = wc - 1;
-    // lane groups (non-CM): a wave of `group`-lane groups, all on the same
-    // columns, group g walking row chunk ty + g (narrow tail strips of a
-    // level keep the wave's lanes busy); group = 64 is one strip
-    const int li = CM ? lane : (lane & (group - 1));
-    const int g = CM ? 0 : lane / group;
-    const int cx0 = CM ? tx * FT_BX_CM : tx * FT_BX, cy0 = (ty + g) * ch;
-    const int cx = CM ? cx0 - 1 + lane : cx0 + li;
-    const int x0 = PD_CELL * min(max(cx, 0), wc - 1);  // lanes past the edges read valid pixels
-    // a group past the level's last row chunk does nothing (empty row range)
-    const int cy_last = cy0 <= max(hc - 2, 0) || cy0 == 0 ? min(cy0 + ch, hc - 1) : cy0 - 1;
-    const int cy_start = (CM && cy0 > 0) ? cy0 - 1 : cy0;
-    const bool own = !CM || (lane >= 1 && lane <= FT_BX_CM && cx < wc);
-    const bool lbp_col = CM ? own : cx < wc && (li < group - 1 || cx == wc - 1);
-    const bool blk_col = CM ? (own && cx < wb) : (li < group - 1 && cx < wb);
-    const bool left_real = cx - 1 >= 0 && cx - 1 < wc, right_real = cx + 1 >= 0 && cx + 1 < wc;
-    float down9[PD_HOG_BINS];  // CM: votes from the row above, gathered per target cell
+    gptr<const uint8_t> img;
+    int w, h, pitch;
+    gptr<float> hog;
+    gptr<uint16_t> hog16;
+    gptr<uint8_t> lbp;
+    gptr<float> cmap;
+    gptr<uint16_t> cmap16;
+    float clip, eps;
+    int hc, wc, hb, wb;
+    int cx;              // the lane's cell column (may lie outside the level)
+    int x0;              // its first pixel, clamped into the level
+    bool own;            // CM: the strip owns the lane's cells
+    const uint32_t* lut;
+    uint32_t* cnt;       // LBP_WORDS words
+    float* vote;         // [slot][lane]: the lanes of a wave hit distinct banks
+
+    __device__ __forceinline__ PixRow row(int y) const { return load_row(img, pitch, w, y, x0); }
+    __device__ __forceinline__ void clear() const {
+        if (DO_LBP) {
 #pragma unroll
-    for (int k = 0; k < PD_HOG_BINS; ++k) down9[k] = 0.0f;
+            for (int k = 0; k < LBP_WORDS; ++k) cnt[k] = 0u;
+        }
+        if (DO_HOG) {
+#pragma unroll
+            for (int k = 0; k < VOTE_SLOTS; ++k) vote[k * FT_W] = 0.0f;
+        }
+    }
+    // the two terms one cell row gives slot (r, c), c in {0, 1}, of the block
+    // starting at this lane's column: own dx = c and the right lane's dx = c - 1
+    static __device__ __forceinline__ float pair(const float (&X)[3][PD_HOG_BINS], int c, int k) {
+        return X[1 + c][k] + __shfl_down(X[c][k], 1, 64);
+    }
     // CM: the 9 votes aimed at this lane's cell from three source columns:
     // own (dx = 0), the right neighbour's dx = -1 and the left's dx = +1
-    auto gather3 = [&](float l, float o, float r) -> float {
+    __device__ __forceinline__ float gather3(float l, float o, float r) const {
         const float fr = __shfl_down(l, 1, 64);
         const float fl = __shfl_up(r, 1, 64);
+        const bool left_real = cx - 1 >= 0 && cx - 1 < wc, right_real = cx + 1 >= 0 && cx + 1 < wc;
         return o + (right_real ? fr : 0.0f) + (left_real ? fl : 0.0f);
-    };
-    auto emit_cell = [&](int row, const float* hist) {
+    }
+    __device__ __forceinline__ void emit_cell(int row, const float* hist) const {
         float ss = 0.0f;
 #pragma unroll
         for (int k = 0; k < PD_HOG_BINS; ++k) ss = fmaf(hist[k], hist[k], ss);
@@ -207,10 +209,10 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
                 o[8] = f32_to_bf16(hist[8] * inv);
             }
         }
-    };
+    }
     // L2-Hys of one block (slots (r, c) in order (0,0), (0,1), (1,0), (1,1)),
     // stored into the planes at block row `row`, column cx
-    auto store_block = [&](float (&v)[PD_HOG_BLOCK], int row) {
+    __device__ __forceinline__ void store_block(float (&v)[PD_HOG_BLOCK], int row) const {
         const float e2 = eps * eps;
         float ss = 0.0f;
 #pragma unroll
@@ -240,38 +242,10 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
                 o += plane;
             }
         }
-    };
-    uint32_t* cnt = &sm.cnt[wave][lane * LBP_WORDS];
-    if (DO_LBP) {
-#pragma unroll
-        for (int k = 0; k < LBP_WORDS; ++k) cnt[k] = 0u;
     }
-    // this lane's vote accumulators, [slot][lane] (slot stride FT_W words, so
-    // the lanes of a wave hit distinct banks)
-    float* vote = &sm.vote[wave][0][lane];
-    if (DO_HOG) {
-#pragma unroll
-        for (int k = 0; k < VOTE_SLOTS; ++k) vote[k * FT_W] = 0.0f;
-    }
-
-    // In registers.  With CM, value (r*3 + c+1)*9 + k is the previous cell
-    // row's partial of dir (dy = r, dx = c); after the top half of the next
-    // row, r = 0 also holds that row's dy = -1 votes (the other term of the
-    // same slots).  Without CM, value (r*2 + c)*9 + k is the sum aimed at slot
-    // (r, c) of the block whose top-left cell is this lane's in the previous
-    // row, from that row's two cells (and, after the top half of the next row,
-    // from the next row's dy = -1 votes).
-    float Pn[CM ? 6 * PD_HOG_BINS : 4 * PD_HOG_BINS];
-    auto PV = [&](int i) -> float& { return Pn[i]; };
-    // the two terms one cell row gives slot (r, c), c in {0, 1}, of the block
-    // starting at this lane's column: own dx = c and the right lane's dx = c - 1
-    auto pair = [&](const float (&X)[3][PD_HOG_BINS], int c, int k) -> float {
-        return X[1 + c][k] + __shfl_down(X[c][k], 1, 64);
-    };
-    float Aa[3][PD_HOG_BINS], Ab[3][PD_HOG_BINS];  // [dx+1][bin] for two target rows
     // target row r's accumulators into X (bin 9 folded into bin 0), then
     // cleared for the next votes
-    auto take = [&](int r, float (&X)[3][PD_HOG_BINS]) {
+    __device__ __forceinline__ void take(int r, float (&X)[3][PD_HOG_BINS]) const {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             float* q = vote + (r * 3 + a) * VOTE_BINS * FT_W;
@@ -281,11 +255,10 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
 #pragma unroll
             for (int k = 0; k < VOTE_BINS; ++k) q[k * FT_W] = 0.0f;
         }
-    };
-
-    // one pixel row: votes into Aa (upper target row) and Ab (lower target row)
-    auto pixel_row = [&](int py, const PixRow& U, const PixRow& C, const PixRow& D, float s0, float s1,
-                         bool count_lbp) {
+    }
+    // one pixel row: votes into the accumulators of the upper and the lower target row
+    __device__ __forceinline__ void pixel_row(const PixRow& U, const PixRow& C, const PixRow& D, float s0, float s1,
+                                              bool count_lbp) const {
         // LBP codes of the row's 8 pixels, four per word (Algorithm 1's
         // neighbours in its bit order: up-left, up, up-right, right,
         // down-right, down, down-left, left)
@@ -308,7 +281,7 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
             const int L = px_at(C, px), Rt = px_at(C, px + 2);
             const int T = px_at(U, px + 1), B = px_at(D, px + 1);
             if (DO_LBP && count_lbp) {
-                const uint32_t e = sm.lut[(code4[px >> 2] >> (8 * (px & 3))) & 255u];
+                const uint32_t e = lut[(code4[px >> 2] >> (8 * (px & 3))) & 255u];
                 // an LDS add: no read of the counter word comes back to the lane
                 __hip_atomic_fetch_add(cnt + (e & 127u), e >> 7, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -354,8 +327,102 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
                     }
             }
         }
-    };
+    }
+    // LBP histogram of cell row cy, and its channels of the cell map
+    __device__ __forceinline__ void store_lbp(int cy) const {
+                        const size_t plane = (size_t)hc * wc;
+                        auto o = lbp + (size_t)cy * wc + cx;
+                        // the 15 counter words once, then one byte store per bin
+                        uint32_t words[LBP_WORDS];
+        #pragma unroll
+                        for (int k = 0; k < LBP_WORDS; ++k) words[k] = cnt[k];
+        #pragma unroll
+                        for (int k = 0; k < PD_LBP_BINS; ++k, o += plane) *o = (uint8_t)(words[k >> 2] >> (8 * (k & 3)));
+                        if (CM && cmap) {
+                            auto c = cmap + ((size_t)PD_HOG_BINS * hc + cy) * wc + cx;
+        #pragma unroll 1
+                            for (int k = 0; k < PD_LBP_BINS; ++k, c += plane)
+                                *c = (float)((cnt[k >> 2] >> (8 * (k & 3))) & 255u) * (1.0f / 64.0f);
+                        }
+                        if (CM && cmap16) {
+                            // channels 9..71: counts / 64 (exact in BF16), then 4 zeros.
+                            // Bytes 18..143 of the cell's 16-byte aligned record: a
+                            // 2-, a 4- and an 8-byte store up to byte 32, then 7
+                            // 16-byte stores
+                            // A count is at most 64, so count / 64 has at most seven
+                            // significant bits: exact in BF16, whose bits are then the
+                            // FP32 value's upper half (no rounding step needed).
+                            const auto cell = cmap16 + ((size_t)cy * wc + cx) * PR_CP1;
+                            auto ch = [&](int c) -> float {  // channel c (9..71) as FP32
+                                const int k = c - PD_HOG_BINS;
+                                return k < PD_LBP_BINS ? (float)((cnt[k >> 2] >> (8 * (k & 3))) & 255u) * (1.0f / 64.0f)
+                                                       : 0.0f;
+                            };
+                            auto two = [&](int c) {  // BF16 bits of channels c, c + 1
+                                return __builtin_amdgcn_perm(__float_as_uint(ch(c + 1)), __float_as_uint(ch(c)), 0x07060302u);
+                            };
+                            cell[9] = (uint16_t)(__float_as_uint(ch(9)) >> 16);
+                            *reinterpret_cast<gptr<uint32_t>>(cell + 10) = two(10);
+                            *reinterpret_cast<gptr<uint2>>(cell + 12) = make_uint2(two(12), two(14));
+        #pragma unroll 1
+                            for (int c = 16; c < PR_CP1; c += 8)
+                                *reinterpret_cast<gptr<uint4>>(cell + c) = make_uint4(two(c), two(c + 2), two(c + 4), two(c + 6));
+                        }
+    }
+};
 
+// With CM the strip also emits the pruner's cell map: per cell, the 9-bin
+// histogram with the full bilinear spatial kernel (every vote aimed at the
+// cell: its own pixels' and its 8 neighbours', Sum_d A[c - d][d]), divided by
+// sqrt(|h|^2 + eps^2), then the 59 LBP counts / 64: FP32 planar
+// [68][hc][wc] (cmap) and/or BF16 channels-last [hc][wc][72] (cmap16).
+// Lanes 1..62 own columns tx*62 .. tx*62 + 61, lanes 0 and 63 are halo, and
+// the strip starts half a cell row early (the downward votes of the row
+// above), so each owned cell sees all of its neighbours' partials.
+template <int FEAT, bool CM = false>
+__device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ img, int w, int h, int pitch,
+                                               gptr<float> __restrict__ hog, gptr<uint16_t> __restrict__ hog16,
+                                               gptr<uint8_t> __restrict__ lbp, gptr<float> __restrict__ cmap,
+                                               gptr<uint16_t> __restrict__ cmap16, int ty, int tx, int ch, float clip,
+                                               float eps, FeatShared& sm, int wave, int group = 64) {
+    constexpr bool DO_HOG = (FEAT & PD_FEAT_HOG) != 0;
+    constexpr bool DO_LBP = (FEAT & PD_FEAT_LBP) != 0;
+    static_assert(!CM || (DO_HOG && DO_LBP), "the cell map needs HOG and LBP");
+    const int lane = threadIdx.x & 63;
+    const int hc = h / PD_CELL, wc = w / PD_CELL;
+    const int hb = hc - 1, wb = wc - 1;
+    // lane groups (non-CM): a wave of `group`-lane groups, all on the same
+    // columns, group g walking row chunk ty + g (narrow tail strips of a
+    // level keep the wave's lanes busy); group = 64 is one strip
+    const int li = CM ? lane : (lane & (group - 1));
+    const int g = CM ? 0 : lane / group;
+    const int cx0 = CM ? tx * FT_BX_CM : tx * FT_BX, cy0 = (ty + g) * ch;
+    const int cx = CM ? cx0 - 1 + lane : cx0 + li;
+    const int x0 = PD_CELL * min(max(cx, 0), wc - 1);  // lanes past the edges read valid pixels
+    // a group past the level's last row chunk does nothing (empty row range)
+    const int cy_last = cy0 <= max(hc - 2, 0) || cy0 == 0 ? min(cy0 + ch, hc - 1) : cy0 - 1;
+    const int cy_start = (CM && cy0 > 0) ? cy0 - 1 : cy0;
+    const bool own = !CM || (lane >= 1 && lane <= FT_BX_CM && cx < wc);
+    const bool lbp_col = CM ? own : cx < wc && (li < group - 1 || cx == wc - 1);
+    const bool blk_col = CM ? (own && cx < wb) : (li < group - 1 && cx < wb);
+    float down9[PD_HOG_BINS];  // CM: votes from the row above, gathered per target cell
+#pragma unroll
+    for (int k = 0; k < PD_HOG_BINS; ++k) down9[k] = 0.0f;
+    const Lane<FEAT, CM> L{img, w, h, pitch, hog, hog16, lbp, cmap, cmap16, clip, eps, hc, wc, hb, wb, cx, x0, own,
+                                    sm.lut, &sm.cnt[wave][lane * LBP_WORDS], &sm.vote[wave][0][lane]};
+    auto pair = [](const float (&X)[3][PD_HOG_BINS], int c, int k) { return Lane<FEAT, CM>::pair(X, c, k); };
+    L.clear();
+
+    // In registers.  With CM, value (r*3 + c+1)*9 + k is the previous cell
+    // row's partial of dir (dy = r, dx = c); after the top half of the next
+    // row, r = 0 also holds that row's dy = -1 votes (the other term of the
+    // same slots).  Without CM, value (r*2 + c)*9 + k is the sum aimed at slot
+    // (r, c) of the block whose top-left cell is this lane's in the previous
+    // row, from that row's two cells (and, after the top half of the next row,
+    // from the next row's dy = -1 votes).
+    float Pn[CM ? 6 * PD_HOG_BINS : 4 * PD_HOG_BINS];
+    auto PV = [&](int i) -> float& { return Pn[i]; };
+    float Aa[3][PD_HOG_BINS], Ab[3][PD_HOG_BINS];  // [dx+1][bin] for two target rows
     // The first cell row's three leading neighbourhood rows.  A cell row's
     // pixel loop ends holding the next cell row's (pixel rows 8 cy + 7 ..
     // 8 cy + 9, inside the image for every cell row but the last), so they
@@ -364,9 +431,9 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
     PixRow U, C, D;
     {
         const int yb0 = PD_CELL * cy_start - 1 + ((CM && cy_start < cy0) ? 4 : 0);
-        U = load_row<ALIGNED>(img, pitch, w, min(max(yb0, 0), h - 1), x0);
-        C = load_row<ALIGNED>(img, pitch, w, min(yb0 + 1, h - 1), x0);
-        D = load_row<ALIGNED>(img, pitch, w, min(yb0 + 2, h - 1), x0);
+        U = L.row(min(max(yb0, 0), h - 1));
+        C = L.row(min(yb0 + 1, h - 1));
+        D = L.row(min(yb0 + 2, h - 1));
     }
     for (int cy = cy_start; cy <= cy_last; ++cy) {
         // CM's extra row above the strip: only its downward votes are needed
@@ -383,15 +450,15 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
         if (!extra) {
 #pragma unroll 1
             for (int py = 0; py < 4; ++py) {
-                const PixRow N = load_row<ALIGNED>(img, pitch, w, min(yb + py + 3, h - 1), x0);
+                const PixRow N = L.row(min(yb + py + 3, h - 1));
                 const float fpy = (float)py;
-                pixel_row(py, U, C, D, (3.5f - fpy) * 0.125f, (4.5f + fpy) * 0.125f, true);
+                L.pixel_row(U, C, D, (3.5f - fpy) * 0.125f, (4.5f + fpy) * 0.125f, true);
                 U = C;
                 C = D;
                 D = N;
             }
         }
-        if (DO_HOG) take(0, Aa);  // the top half's votes towards cell row -1
+        if (DO_HOG) L.take(0, Aa);  // the top half's votes towards cell row -1
         if (DO_HOG) {
             if (cy > cy_start && !CM) {  // fold the dy = -1 votes into the top slots
 #pragma unroll
@@ -417,11 +484,11 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
                     float hist[PD_HOG_BINS];
 #pragma unroll
                     for (int k = 0; k < PD_HOG_BINS; ++k)
-                        hist[k] = down9[k] + gather3(PV(0 * 9 + k), PV(1 * 9 + k), PV(2 * 9 + k));
-                    if (cy - 1 >= cy0) emit_cell(cy - 1, hist);
+                        hist[k] = down9[k] + L.gather3(PV(0 * 9 + k), PV(1 * 9 + k), PV(2 * 9 + k));
+                    if (cy - 1 >= cy0) L.emit_cell(cy - 1, hist);
 #pragma unroll
                     for (int k = 0; k < PD_HOG_BINS; ++k)
-                        down9[k] = gather3(PV(3 * 9 + k), PV(4 * 9 + k), PV(5 * 9 + k));
+                        down9[k] = L.gather3(PV(3 * 9 + k), PV(4 * 9 + k), PV(5 * 9 + k));
                 }
             }
 #pragma unroll
@@ -432,63 +499,26 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
         // bottom half: pixel rows 4..7 vote towards cell rows +1 (Aa) and 0 (Ab)
 #pragma unroll 1
         for (int py = 4; py < 8; ++py) {
-            const PixRow N = load_row<ALIGNED>(img, pitch, w, min(yb + py + 3, h - 1), x0);
+            const PixRow N = L.row(min(yb + py + 3, h - 1));
             const float fpy = (float)py;
-            pixel_row(py, U, C, D, (fpy - 3.5f) * 0.125f, (11.5f - fpy) * 0.125f, !extra);
+            L.pixel_row(U, C, D, (fpy - 3.5f) * 0.125f, (11.5f - fpy) * 0.125f, !extra);
             U = C;
             C = D;
             D = N;
         }
         if (DO_HOG) {  // the bottom half's votes towards cell rows +1 and 0
-            take(0, Aa);
-            take(1, Ab);
+            L.take(0, Aa);
+            L.take(1, Ab);
         }
 
         // LBP histogram of this cell row
         if (DO_LBP) {
             const bool own_row = cy >= cy0 && (cy < cy0 + ch || cy == hc - 1);
             if (own_row && lbp_col) {
-                const size_t plane = (size_t)hc * wc;
-                auto o = lbp + (size_t)cy * wc + cx;
-                // the 15 counter words once, then one byte store per bin
-                uint32_t words[LBP_WORDS];
-#pragma unroll
-                for (int k = 0; k < LBP_WORDS; ++k) words[k] = cnt[k];
-#pragma unroll
-                for (int k = 0; k < PD_LBP_BINS; ++k, o += plane) *o = (uint8_t)(words[k >> 2] >> (8 * (k & 3)));
-                if (CM && cmap) {
-                    auto c = cmap + ((size_t)PD_HOG_BINS * hc + cy) * wc + cx;
-#pragma unroll 1
-                    for (int k = 0; k < PD_LBP_BINS; ++k, c += plane)
-                        *c = (float)((cnt[k >> 2] >> (8 * (k & 3))) & 255u) * (1.0f / 64.0f);
-                }
-                if (CM && cmap16) {
-                    // channels 9..71: counts / 64 (exact in BF16), then 4 zeros.
-                    // Bytes 18..143 of the cell's 16-byte aligned record: a
-                    // 2-, a 4- and an 8-byte store up to byte 32, then 7
-                    // 16-byte stores
-                    // A count is at most 64, so count / 64 has at most seven
-                    // significant bits: exact in BF16, whose bits are then the
-                    // FP32 value's upper half (no rounding step needed).
-                    const auto cell = cmap16 + ((size_t)cy * wc + cx) * PR_CP1;
-                    auto ch = [&](int c) -> float {  // channel c (9..71) as FP32
-                        const int k = c - PD_HOG_BINS;
-                        return k < PD_LBP_BINS ? (float)((cnt[k >> 2] >> (8 * (k & 3))) & 255u) * (1.0f / 64.0f)
-                                               : 0.0f;
-                    };
-                    auto two = [&](int c) {  // BF16 bits of channels c, c + 1
-                        return __builtin_amdgcn_perm(__float_as_uint(ch(c + 1)), __float_as_uint(ch(c)), 0x07060302u);
-                    };
-                    cell[9] = (uint16_t)(__float_as_uint(ch(9)) >> 16);
-                    *reinterpret_cast<gptr<uint32_t>>(cell + 10) = two(10);
-                    *reinterpret_cast<gptr<uint2>>(cell + 12) = make_uint2(two(12), two(14));
-#pragma unroll 1
-                    for (int c = 16; c < PR_CP1; c += 8)
-                        *reinterpret_cast<gptr<uint4>>(cell + c) = make_uint4(two(c), two(c + 2), two(c + 4), two(c + 6));
-                }
+                L.store_lbp(cy);
             }
 #pragma unroll
-            for (int k = 0; k < LBP_WORDS; ++k) cnt[k] = 0u;
+            for (int k = 0; k < LBP_WORDS; ++k) L.cnt[k] = 0u;
         }
 
         if (DO_HOG) {
@@ -510,7 +540,7 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
                     v[2 * 9 + k] = PV(2 * 9 + k) + S[0][k];
                     v[3 * 9 + k] = PV(3 * 9 + k) + S[1][k];
                 }
-                if (blk_col) store_block(v, cy - 1);
+                if (blk_col) L.store_block(v, cy - 1);
             }
             if (cy > cy0 && CM) {
                 float v[PD_HOG_BLOCK];
@@ -521,7 +551,7 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
                     v[2 * 9 + k] = (PV(4 * 9 + k) + __shfl_down(PV(3 * 9 + k), 1, 64)) + S[0][k];
                     v[3 * 9 + k] = (PV(5 * 9 + k) + __shfl_down(PV(4 * 9 + k), 1, 64)) + S[1][k];
                 }
-                if (blk_col) store_block(v, cy - 1);
+                if (blk_col) L.store_block(v, cy - 1);
             }
             if (cy < cy_last && !CM) {  // this row's slot sums for the next row's blocks
 #pragma unroll
@@ -546,79 +576,253 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
     if (CM && cy_last == hc - 1) {  // the level's last cell row: no row below it
         float hist[PD_HOG_BINS];
 #pragma unroll
-        for (int k = 0; k < PD_HOG_BINS; ++k) hist[k] = down9[k] + gather3(Ab[0][k], Ab[1][k], Ab[2][k]);
-        emit_cell(hc - 1, hist);
+        for (int k = 0; k < PD_HOG_BINS; ++k) hist[k] = down9[k] + L.gather3(Ab[0][k], Ab[1][k], Ab[2][k]);
+        L.emit_cell(hc - 1, hist);
+    }
+}
+
+// ---- few strips: a wave per cell row ---------------------------------------
+// A strip walks its cell rows in turn, 1.8 us per pixel row of its 64 cells (the
+// votes' LDS chains, with nothing else on the SIMD to cover them), so a launch
+// with few strips takes as long as one of them: 135 us for 8 block rows, for a
+// 320x240 frame as for a 1242x375 one.  In this form they take 20 and 32 us, a
+// level's cell map 25 us (from 180).  Here a workgroup's waves
+// take one cell row each (lane groups: 64 / width rows each) and pass what the
+// strip keeps in registers from one row to the next through LDS, in the bytes
+// of the vote accumulators.  The sums are the strip's, term by term: the same
+// bits.  A workgroup's first row is its neighbour's last one (with the cell
+// map, one more above), so it computes R rows for R - 1 block rows (R - 2), and
+// long launches keep the strips.
+template <int RW>
+struct RowShared {
+    uint32_t lut[256];
+    uint32_t cnt[RW][FT_W * LBP_WORDS];
+    float vote[RW][VOTE_SLOTS][FT_W];
+};
+
+// Block rows (cell rows without HOG) of a workgroup of R cell rows.
+template <int FEAT, bool CM>
+__host__ __device__ constexpr int row_chunk(int R) {
+    return CM ? R - 2 : (FEAT & PD_FEAT_HOG) ? R - 1 : R;
+}
+
+template <int FEAT, bool CM, int RW>
+__device__ __forceinline__ void features_rows(const LevelItem& it, int cy0, int tx, int width, float clip, float eps,
+                                              RowShared<RW>& sm) {
+    constexpr bool DO_HOG = (FEAT & PD_FEAT_HOG) != 0, DO_LBP = (FEAT & PD_FEAT_LBP) != 0;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = it.w, h = it.h, hc = it.hc, wc = it.wc, hb = hc - 1, wb = wc - 1;
+    const int G = CM ? 1 : 64 / width, R = RW * G;
+    const int li = CM ? lane : lane & (width - 1), g = CM ? 0 : lane / width;
+    const int rr = wave * G + g;                     // the lane's row in the workgroup
+    const int cy = (CM ? cy0 - 1 : cy0) + rr;        // and in the level (may lie outside)
+    const int cx = CM ? tx * FT_BX_CM - 1 + lane : tx * FT_BX + li;
+    const int x0 = PD_CELL * min(max(cx, 0), wc - 1);
+    const bool own = !CM || (lane >= 1 && lane <= FT_BX_CM && cx < wc);
+    const bool lbp_col = CM ? own : cx < wc && (li < width - 1 || cx == wc - 1);
+    const bool blk_col = CM ? (own && cx < wb) : (li < width - 1 && cx < wb);
+    const bool in = cy >= 0 && cy < hc;
+    // the rows whose LBP counts (and cell map) this workgroup stores
+    const bool own_row = in && (CM ? rr >= 1 && rr < R - 1 : !DO_HOG || rr < R - 1 || cy == hc - 1);
+    const Lane<FEAT, CM> L{gmem(it.pyr), w, h, it.pitch, gmem(it.hog), gmem(it.hog16), gmem(it.lbp), gmem(it.cmap),
+                           gmem(it.cmap16), clip, eps, hc, wc, hb, wb, cx, x0, own, sm.lut,
+                           &sm.cnt[wave][lane * LBP_WORDS], &sm.vote[wave][0][lane]};
+    float T[3][PD_HOG_BINS], D9[3][PD_HOG_BINS], O[3][PD_HOG_BINS];  // votes towards cell rows cy - 1, cy + 1 and cy
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int k = 0; k < PD_HOG_BINS; ++k) T[a][k] = D9[a][k] = O[a][k] = 0.0f;
+    if (__any(in)) {
+        L.clear();
+        const bool count = __any(own_row);
+        const int yb = PD_CELL * min(max(cy, 0), hc - 1) - 1;  // pixel row of neighbourhood row 0
+        PixRow U = L.row(max(yb, 0)), C = L.row(yb + 1), D = L.row(min(yb + 2, h - 1));
+#pragma unroll 1
+        for (int py = 0; py < 4; ++py) {
+            const PixRow N = L.row(min(yb + py + 3, h - 1));
+            const float fpy = (float)py;
+            L.pixel_row(U, C, D, (3.5f - fpy) * 0.125f, (4.5f + fpy) * 0.125f, count);
+            U = C;
+            C = D;
+            D = N;
+        }
+        if (DO_HOG) L.take(0, T);
+#pragma unroll 1
+        for (int py = 4; py < 8; ++py) {
+            const PixRow N = L.row(min(yb + py + 3, h - 1));
+            const float fpy = (float)py;
+            L.pixel_row(U, C, D, (fpy - 3.5f) * 0.125f, (11.5f - fpy) * 0.125f, count);
+            U = C;
+            C = D;
+            D = N;
+        }
+        if (DO_HOG) {
+            L.take(0, D9);
+            L.take(1, O);
+        }
+        if (DO_LBP && own_row && lbp_col) L.store_lbp(cy);
+    }
+    if (!DO_HOG) return;
+    if (CM && !in) {  // rows outside the level vote for nothing
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int k = 0; k < PD_HOG_BINS; ++k) T[a][k] = D9[a][k] = O[a][k] = 0.0f;
+    }
+    // what the next row needs, through this wave's accumulator bytes
+    float* const mine = &sm.vote[wave][0][lane];
+    float S[2][PD_HOG_BINS];
+#pragma unroll
+    for (int k = 0; k < PD_HOG_BINS; ++k) {
+        S[0][k] = L.pair(O, 0, k);
+        S[1][k] = L.pair(O, 1, k);
+        if constexpr (CM) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                mine[(a * 9 + k) * FT_W] = O[a][k];
+                mine[((3 + a) * 9 + k) * FT_W] = D9[a][k];
+            }
+        } else {
+            mine[k * FT_W] = S[0][k];
+            mine[(9 + k) * FT_W] = S[1][k];
+            mine[(18 + k) * FT_W] = L.pair(D9, 0, k);
+            mine[(27 + k) * FT_W] = L.pair(D9, 1, k);
+        }
+    }
+    __syncthreads();
+    if (__all(rr == 0)) return;
+    const int pr = max(rr - 1, 0);
+    const float* const prev = &sm.vote[pr / G][0][(pr % G) * width + li];
+    float v[PD_HOG_BLOCK];  // the block of rows cy - 1 and cy, slots top to bottom
+    if constexpr (CM) {
+        float Op[3][PD_HOG_BINS], Dp[3][PD_HOG_BINS];
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int k = 0; k < PD_HOG_BINS; ++k) {
+                Op[a][k] = prev[(a * 9 + k) * FT_W];
+                Dp[a][k] = prev[((3 + a) * 9 + k) * FT_W];
+            }
+#pragma unroll
+        for (int k = 0; k < PD_HOG_BINS; ++k) {
+            v[0 * 9 + k] = L.pair(Op, 0, k) + L.pair(T, 0, k);
+            v[1 * 9 + k] = L.pair(Op, 1, k) + L.pair(T, 1, k);
+            v[2 * 9 + k] = L.pair(Dp, 0, k) + S[0][k];
+            v[3 * 9 + k] = L.pair(Dp, 1, k) + S[1][k];
+        }
+        // cell row cy - 1 (the votes of rows cy - 2, cy - 1 and cy), and the
+        // level's last row, which nothing below votes for
+        float hist[PD_HOG_BINS];
+        if (rr >= 2 && cy - 1 < hc) {
+            const float* const above = &sm.vote[rr - 2][0][lane];
+#pragma unroll
+            for (int k = 0; k < PD_HOG_BINS; ++k)
+                hist[k] = L.gather3(above[(27 + k) * FT_W], above[(36 + k) * FT_W], above[(45 + k) * FT_W]) +
+                          L.gather3(Op[0][k] + T[0][k], Op[1][k] + T[1][k], Op[2][k] + T[2][k]);
+            if (cy < hc) L.emit_cell(cy - 1, hist);
+        }
+        if (cy == hc - 1 && rr < R - 1) {
+#pragma unroll
+            for (int k = 0; k < PD_HOG_BINS; ++k)
+                hist[k] = L.gather3(Dp[0][k], Dp[1][k], Dp[2][k]) + L.gather3(O[0][k], O[1][k], O[2][k]);
+            L.emit_cell(cy, hist);
+        }
+        if (rr >= 2 && cy < hc && blk_col) L.store_block(v, cy - 1);
+    } else {
+#pragma unroll
+        for (int k = 0; k < PD_HOG_BINS; ++k) {
+            v[0 * 9 + k] = prev[k * FT_W] + L.pair(T, 0, k);
+            v[1 * 9 + k] = prev[(9 + k) * FT_W] + L.pair(T, 1, k);
+            v[2 * 9 + k] = prev[(18 + k) * FT_W] + S[0][k];
+            v[3 * 9 + k] = prev[(27 + k) * FT_W] + S[1][k];
+        }
+        if (rr >= 1 && cy < hc && blk_col) L.store_block(v, cy - 1);
     }
 }
 
 // Indexed by the bit-reversed code that lbp_codes4 produces.
-__device__ inline void init_lut(FeatShared& sm) {
-    for (int c = threadIdx.x; c < 256; c += FT_WAVES * 64) {
+template <int THREADS>
+__device__ inline void init_lut(uint32_t (&lut)[256]) {
+    for (int c = threadIdx.x; c < 256; c += THREADS) {
         const int b = kLbp.bin[__brev(c) >> 24];
-        sm.lut[c] = ((1u << (8 * (b & 3))) << 7) | (uint32_t)(b >> 2);
+        lut[c] = ((1u << (8 * (b & 3))) << 7) | (uint32_t)(b >> 2);
     }
+    __syncthreads();
 }
 
-template <int FEAT, bool ALIGNED>
-__global__ void __launch_bounds__(FT_WAVES * 64) features_single_kernel(LevelItem it, float clip, float eps) {
-    __shared__ FeatShared sm;
-    init_lut(sm);
-    __syncthreads();
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int task = blockIdx.x * FT_WAVES + wave;
-    const int ntx = feat_tiles_x(it.wc);
-    if (task >= ntx * feat_tiles_y(it.hc)) return;
-    features_strip<FEAT, ALIGNED>(gmem(it.pyr), it.w, it.h, it.pitch, gmem(it.hog), gmem(it.hog16), gmem(it.lbp),
-                                  nullptr, nullptr, task / ntx, task % ntx, FT_CH, clip, eps, sm, wave);
+// One image: block x = strip, block y = chunk of rows.
+template <int FEAT, bool CM, int RW>
+__global__ void __launch_bounds__(RW * 64) features_rows_single_kernel(LevelItem it, float clip, float eps) {
+    __shared__ RowShared<RW> sm;
+    int width = 64;
+    if (!CM) {
+        const int left = max(it.wc - 1, 1) - (int)blockIdx.x * FT_BX;  // block columns from this strip on
+        while (width > 2 && width / 2 - 1 >= left) width /= 2;
+    }
+    const int cy0 = blockIdx.y * row_chunk<FEAT, CM>(RW * (64 / width));
+    if (cy0 > 0 && cy0 >= ((FEAT & PD_FEAT_HOG) && !CM ? it.hc - 1 : it.hc)) return;
+    init_lut<RW * 64>(sm.lut);
+    features_rows<FEAT, CM, RW>(it, cy0, blockIdx.x, width, clip, eps, sm);
 }
 
-template <bool ALIGNED>
-__global__ void __launch_bounds__(FT_WAVES * 64) cellmap_single_kernel(LevelItem it, float clip, float eps) {
-    __shared__ FeatShared sm;
-    init_lut(sm);
-    __syncthreads();
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int task = blockIdx.x * FT_WAVES + wave;
-    const int ntx = feat_tiles_x_cm(it.wc);
-    if (task >= ntx * feat_tiles_y(it.hc)) return;
-    features_strip<PD_FEAT_HOG | PD_FEAT_LBP, ALIGNED, true>(
-        gmem(it.pyr), it.w, it.h, it.pitch, gmem(it.hog), gmem(it.hog16), gmem(it.lbp), gmem(it.cmap),
-        gmem(it.cmap16), task / ntx, task % ntx, FT_CH, clip, eps, sm, wave);
+// Table entry: item, ty = the first cell row, tx = strip, pad = lane-group
+// width; block y takes one of its FR_SPAN chunks of rows.
+template <int FEAT, int RW>
+__global__ void __launch_bounds__(RW * 64) features_rows_table_kernel(const LevelItem* __restrict__ items,
+                                                                      const Tile* __restrict__ tiles, float clip,
+                                                                      float eps) {
+    __shared__ RowShared<RW> sm;
+    const Tile tl = tiles[blockIdx.x];
+    const LevelItem& it = items[tl.item];
+    const int cy0 = tl.ty + blockIdx.y * row_chunk<FEAT, false>(RW * (64 / tl.pad));
+    if (cy0 > 0 && cy0 >= ((FEAT & PD_FEAT_HOG) ? it.hc - 1 : it.hc)) return;
+    init_lut<RW * 64>(sm.lut);
+    features_rows<FEAT, false, RW>(it, cy0, tl.tx, tl.pad, clip, eps, sm);
 }
 
 __global__ void __launch_bounds__(FT_WAVES * 64) cellmap_table_kernel(const LevelItem* __restrict__ items,
                                                             const Tile* __restrict__ tiles, int n_tiles, int ch,
                                                             float clip, float eps) {
     __shared__ FeatShared sm;
-    init_lut(sm);
-    __syncthreads();
+    init_lut<FT_WAVES * 64>(sm.lut);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int task = blockIdx.x * FT_WAVES + wave; task < n_tiles; task += gridDim.x * FT_WAVES) {
         const Tile tl = tiles[task];
         const LevelItem& it = items[tl.item];
-        features_strip<PD_FEAT_HOG | PD_FEAT_LBP, true, true>(gmem(it.pyr), it.w, it.h, it.pitch, gmem(it.hog),
-                                                              gmem(it.hog16), gmem(it.lbp), gmem(it.cmap),
-                                                              gmem(it.cmap16), tl.ty, tl.tx, ch, clip, eps, sm, wave);
+        features_strip<PD_FEAT_HOG | PD_FEAT_LBP, true>(gmem(it.pyr), it.w, it.h, it.pitch, gmem(it.hog),
+                                                        gmem(it.hog16), gmem(it.lbp), gmem(it.cmap), gmem(it.cmap16),
+                                                        tl.ty, tl.tx, ch, clip, eps, sm, wave);
     }
 }
 
-// The table launch requires 8-byte aligned level rows (pd_detect copies
-// misaligned frames into the pyramid buffer).
 template <int FEAT>
 __global__ void __launch_bounds__(FT_WAVES * 64) features_table_kernel(const LevelItem* __restrict__ items,
                                                              const Tile* __restrict__ tiles, int n_tiles, int ch,
                                                              float clip, float eps) {
     __shared__ FeatShared sm;
-    init_lut(sm);
-    __syncthreads();
+    init_lut<FT_WAVES * 64>(sm.lut);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // strips are independent per wave; a capped grid loops over them
     for (int task = blockIdx.x * FT_WAVES + wave; task < n_tiles; task += gridDim.x * FT_WAVES) {
         const Tile tl = tiles[task];
         const LevelItem& it = items[tl.item];
-        features_strip<FEAT, true>(gmem(it.pyr), it.w, it.h, it.pitch, gmem(it.hog), gmem(it.hog16), gmem(it.lbp),
-                                   nullptr, nullptr, tl.ty, tl.tx, ch, clip, eps, sm, wave, tl.pad);
+        features_strip<FEAT>(gmem(it.pyr), it.w, it.h, it.pitch, gmem(it.hog), gmem(it.hog16), gmem(it.lbp), nullptr,
+                             nullptr, tl.ty, tl.tx, ch, clip, eps, sm, wave, tl.pad);
     }
+}
+
+// One image in strips of FT_CH block rows (cell map: of cell rows).
+template <int FEAT, bool CM>
+__global__ void __launch_bounds__(FT_WAVES * 64) features_single_kernel(LevelItem it, float clip, float eps) {
+    __shared__ FeatShared sm;
+    init_lut<FT_WAVES * 64>(sm.lut);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int task = blockIdx.x * FT_WAVES + wave;
+    const int ntx = CM ? feat_tiles_x_cm(it.wc) : feat_tiles_x(it.wc);
+    if (task >= ntx * feat_tiles_y(it.hc)) return;
+    features_strip<FEAT, CM>(gmem(it.pyr), it.w, it.h, it.pitch, gmem(it.hog), gmem(it.hog16), gmem(it.lbp),
+                             CM ? gmem(it.cmap) : nullptr, CM ? gmem(it.cmap16) : nullptr, task / ntx, task % ntx,
+                             FT_CH, clip, eps, sm, wave);
 }
 
 // Algorithm 1 on its own: one thread per pixel (used to check the codes).
@@ -641,17 +845,19 @@ __global__ void __launch_bounds__(256) lbp_codes_kernel(const uint8_t* __restric
     codes[(size_t)y * codes_pitch + x] = (uint8_t)code;
 }
 
-template <int FEAT, bool ALIGNED>
+template <int FEAT, bool CM>
 hipError_t feat_single(const LevelItem& it, float clip, float eps, hipStream_t s) {
-    const int n = feat_tiles_x(it.wc) * feat_tiles_y(it.hc);
-    features_single_kernel<FEAT, ALIGNED><<<ceil_div(n, FT_WAVES), FT_WAVES * 64, 0, s>>>(it, clip, eps);
+    const int ntx = CM ? feat_tiles_x_cm(it.wc) : feat_tiles_x(it.wc);
+    if ((int64_t)ntx * it.hc <= FR_MAX_ROWS) {
+        constexpr int RW = 4;
+        const int chunk = row_chunk<FEAT, CM>(RW);
+        const int rows = (FEAT & PD_FEAT_HOG) && !CM ? std::max(it.hc - 1, 1) : it.hc;
+        features_rows_single_kernel<FEAT, CM, RW><<<dim3(ntx, ceil_div(rows, chunk)), RW * 64, 0, s>>>(it, clip, eps);
+    } else {
+        const int n = ntx * feat_tiles_y(it.hc);
+        features_single_kernel<FEAT, CM><<<ceil_div(n, FT_WAVES), FT_WAVES * 64, 0, s>>>(it, clip, eps);
+    }
     return hipGetLastError();
-}
-
-template <int FEAT>
-hipError_t feat_single_any(const LevelItem& it, float clip, float eps, hipStream_t s) {
-    const bool aligned = (((uintptr_t)it.pyr | (uintptr_t)it.pitch) & 7) == 0;
-    return aligned ? feat_single<FEAT, true>(it, clip, eps, s) : feat_single<FEAT, false>(it, clip, eps, s);
 }
 
 template <int FEAT>
@@ -663,15 +869,33 @@ hipError_t feat_table(const LevelItem* items, const Tile* tiles, int n_tiles, fl
     return hipGetLastError();
 }
 
+template <int FEAT>
+hipError_t feat_rows_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip, float eps,
+                           hipStream_t s) {
+    features_rows_table_kernel<FEAT, FR_WAVES><<<dim3(n_tiles, FR_SPAN), FR_WAVES * 64, 0, s>>>(items, tiles, clip, eps);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+int feat_rows_chunk(int features, int width) {
+    const int R = FR_WAVES * (64 / width);
+    return (features & PD_FEAT_HOG) ? row_chunk<PD_FEAT_HOG, false>(R) : row_chunk<PD_FEAT_LBP, false>(R);
+}
+
+hipError_t launch_features_rows_table(const LevelItem* items, const Tile* tiles, int n_tiles, int features,
+                                      float clip, float eps, hipStream_t s) {
+    if (n_tiles <= 0) return hipSuccess;
+    switch (features & (PD_FEAT_HOG | PD_FEAT_LBP)) {
+        case PD_FEAT_HOG: return feat_rows_table<PD_FEAT_HOG>(items, tiles, n_tiles, clip, eps, s);
+        case PD_FEAT_LBP: return feat_rows_table<PD_FEAT_LBP>(items, tiles, n_tiles, clip, eps, s);
+        default: return feat_rows_table<PD_FEAT_HOG | PD_FEAT_LBP>(items, tiles, n_tiles, clip, eps, s);
+    }
+}
 
 hipError_t launch_features_cellmap_single(const LevelItem& it, float clip, float eps, hipStream_t s) {
     if (it.hc <= 0 || it.wc <= 0) return hipSuccess;
-    const int n = feat_tiles_x_cm(it.wc) * feat_tiles_y(it.hc);
-    const bool aligned = (((uintptr_t)it.pyr | (uintptr_t)it.pitch) & 7) == 0;
-    if (aligned) cellmap_single_kernel<true><<<ceil_div(n, FT_WAVES), FT_WAVES * 64, 0, s>>>(it, clip, eps);
-    else cellmap_single_kernel<false><<<ceil_div(n, FT_WAVES), FT_WAVES * 64, 0, s>>>(it, clip, eps);
-    return hipGetLastError();
+    return feat_single<PD_FEAT_HOG | PD_FEAT_LBP, true>(it, clip, eps, s);
 }
 
 hipError_t launch_features_cellmap_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip,
@@ -693,9 +917,9 @@ hipError_t launch_lbp_codes(const uint8_t* img, int w, int h, int pitch, uint8_t
 hipError_t launch_features_single(const LevelItem& it, int features, float clip, float eps, hipStream_t s) {
     if (it.hc <= 0 || it.wc <= 0) return hipSuccess;
     switch (features & (PD_FEAT_HOG | PD_FEAT_LBP)) {
-        case PD_FEAT_HOG: return feat_single_any<PD_FEAT_HOG>(it, clip, eps, s);
-        case PD_FEAT_LBP: return feat_single_any<PD_FEAT_LBP>(it, clip, eps, s);
-        case PD_FEAT_HOG | PD_FEAT_LBP: return feat_single_any<PD_FEAT_HOG | PD_FEAT_LBP>(it, clip, eps, s);
+        case PD_FEAT_HOG: return feat_single<PD_FEAT_HOG, false>(it, clip, eps, s);
+        case PD_FEAT_LBP: return feat_single<PD_FEAT_LBP, false>(it, clip, eps, s);
+        case PD_FEAT_HOG | PD_FEAT_LBP: return feat_single<PD_FEAT_HOG | PD_FEAT_LBP, false>(it, clip, eps, s);
         default: return hipSuccess;
     }
 }

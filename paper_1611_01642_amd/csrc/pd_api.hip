@@ -502,6 +502,7 @@ struct DetectRun {
     int nrs = 0, nft = 0, nsc = 0, ncp = 0;  // tiles in use
     XcdLists xs{};     // FP32 scoring: the band table's per-XCD lists
     int s32_grid = 0;  // and its launch width
+    bool feat_rows = false;  // features with a wave per cell row (few strips)
     int s32_pairs = 0;  // FP32 scoring by the wave kernel: row pairs per wave (0: the band kernel)
     int32_t* s32_ctr = nullptr;
     float* s32_pack = nullptr;
@@ -532,7 +533,7 @@ struct DetectRun {
 // (L.table_bytes), laid out as they are uploaded to device memory `tbl`: the
 // start of the workspace `ws` for pd_detect, a graph's own buffer for a
 // captured graph.  Every other buffer is in `ws`.
-void fill_tables(const pd_frame* frames, int n_frames, int n_models, const Tuning& tu, const DetectLayout& L,
+void fill_tables(const pd_frame* frames, int n_frames, int n_models, int features, const Tuning& tu, const DetectLayout& L,
                  uint8_t* ws, uint8_t* tbl, uint8_t* stage, DetectRun& R) {
     uint8_t* data = ws + L.off_data;
     std::memset(stage, 0, (size_t)L.table_bytes);
@@ -546,6 +547,10 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, const Tunin
     Tile* t_cp = t_sc + L.n_sc;
     Tile* t_pr = t_cp + L.n_cp;
     int q = 0, nrs = 0, nft = 0, nsc = 0, ncp = 0, npr = 0;
+    int64_t strip_rows = 0;
+    for (size_t k = 0; k < L.sizes.size(); k += 2)
+        strip_rows += (int64_t)feat_tiles_x(L.sizes[k] / PD_CELL) * (L.sizes[k + 1] / PD_CELL);
+    R.feat_rows = !L.prune && strip_rows <= FR_MAX_ROWS;
     for (int f = 0; f < n_frames; ++f) {
         geoms[f].n_levels = L.level_count[f];
         geoms[f].cand_off = L.cand_off[f];
@@ -592,12 +597,20 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, const Tunin
                 const int wb = it.wc - 1;
                 const int full = wb > 0 ? wb / FT_BX : 0;
                 const int tail = wb > 0 ? wb - full * FT_BX : 0;
-                for (int ty = 0; ty < fty; ++ty)
-                    for (int tx = 0; tx < full; ++tx) t_ft[nft++] = Tile{q, ty, tx, 64};
-                if (tail > 0 || full == 0) {
-                    int width = 2;
-                    while (width - 1 < std::max(tail, 1)) width *= 2;
-                    for (int ty = 0; ty < fty; ty += 64 / width) t_ft[nft++] = Tile{q, ty, full, width};
+                int width = 2;
+                while (width - 1 < std::max(tail, 1)) width *= 2;
+                const bool narrow = tail > 0 || full == 0;
+                if (R.feat_rows) {  // entries of FR_SPAN workgroups
+                    for (int tx = 0; tx < full + narrow; ++tx) {
+                        const int wd = tx < full ? 64 : width;
+                        const int step = FR_SPAN * feat_rows_chunk(features, wd);
+                        const int rows = (features & PD_FEAT_HOG) ? std::max(it.hc - 1, 1) : it.hc;
+                        for (int y = 0; y < rows; y += step) t_ft[nft++] = Tile{q, y, tx, wd};
+                    }
+                } else {
+                    for (int ty = 0; ty < fty; ++ty)
+                        for (int tx = 0; tx < full; ++tx) t_ft[nft++] = Tile{q, ty, tx, 64};
+                    for (int ty = 0; narrow && ty < fty; ty += 64 / width) t_ft[nft++] = Tile{q, ty, full, width};
                 }
             }
             if (L.prune) {
@@ -617,7 +630,7 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, const Tunin
             for (int c = 0; c < ceil_div(it.nx * it.ny, CP_N); ++c) t_cp[ncp++] = Tile{q, 0, c, 0};
         }
     }
-    if (nft > 1) {
+    if (nft > 1 && !R.feat_rows) {
         // feature strips longest first (cell rows walked; with the cell map,
         // one more above all but the first), so that the launch ends on its
         // shortest strips: a counting sort, stable within a length
@@ -773,10 +786,11 @@ int enqueue_detect(const DetectRun& R, const DetectLayout& L, const Tuning& tu, 
         return enqueue_decide(R, L, weights, bias, n_models, params, thresholds, n_frames, boxes, cap, counts, marks,
                               R.kth, false, s);
     }
-    if ((rc = hip_status(launch_features_table(R.items, R.t_ft, R.nft, params->features, params->clip, params->eps,
-                                               tu, s),
-                         "features")))
-        return rc;
+    const hipError_t e = R.feat_rows ? launch_features_rows_table(R.items, R.t_ft, R.nft, params->features, params->clip,
+                                                                  params->eps, s)
+                                     : launch_features_table(R.items, R.t_ft, R.nft, params->features, params->clip,
+                                                             params->eps, tu, s);
+    if ((rc = hip_status(e, "features"))) return rc;
     marks.mark(PD_STAGE_SCORE, s);
     bool decided = false;
     if (L.rowgemm) {
@@ -1264,7 +1278,7 @@ int pd_detect(const pd_frame* frames, int n_frames, const float* weights, const 
         slot.size = want;
     }
     DetectRun R;
-    fill_tables(frames, n_frames, n_models, tuning_of(params), L, static_cast<uint8_t*>(workspace),
+    fill_tables(frames, n_frames, n_models, params->features, tuning_of(params), L, static_cast<uint8_t*>(workspace),
                 static_cast<uint8_t*>(workspace), static_cast<uint8_t*>(slot.host), R);
 
     int rc;
@@ -1310,7 +1324,7 @@ int pd_graph_create(const pd_frame* frames, int n_frames, const float* weights, 
         return rc;
     }
     DetectRun R;
-    fill_tables(frames, n_frames, n_models, tuning_of(params), L, static_cast<uint8_t*>(workspace),
+    fill_tables(frames, n_frames, n_models, params->features, tuning_of(params), L, static_cast<uint8_t*>(workspace),
                 static_cast<uint8_t*>(g->tables), host.data(), R);
     rc = hip_status(hipMemcpyAsync(g->tables, host.data(), host.size(), hipMemcpyHostToDevice, s), "table upload");
     if (!rc) rc = hip_status(hipStreamSynchronize(s), "table upload");
@@ -1557,7 +1571,7 @@ int pd::detect_on_workspace(const pd_frame* frames, int n_frames, const float* w
     std::vector<uint8_t> host((size_t)L.table_bytes);
     DetectRun R;
     uint8_t* ws = static_cast<uint8_t*>(workspace);
-    fill_tables(frames, n_frames, n_models, tuning_of(params), L, ws, ws, host.data(), R);
+    fill_tables(frames, n_frames, n_models, params->features, tuning_of(params), L, ws, ws, host.data(), R);
     // only the entries in use: the items, each tile list's used prefix (FP32
     // half-height score tiles follow the others), the NMS geometry and the
     // per-frame item index

@@ -88,6 +88,13 @@ constexpr int FT_W = 64;
 constexpr int FT_BX = 63;
 constexpr int FT_CH = 8;
 constexpr int FT_WAVES = 4;  // waves (independent strips) per workgroup
+// features of few strips: a wave per cell row
+constexpr int FR_WAVES = 4;           // cell rows (of 64 lanes) per workgroup
+constexpr int FR_SPAN = 8;            // workgroups per table entry
+// strip rows (64 cells of one cell row) of a launch at most: about 14 pyramids
+// of 1242x375, where the two forms meet (8 frames: 100 us against 145 in
+// strips; 12: 137 and 148; 16: 180 and 194; 24: 259 and 201)
+constexpr int64_t FR_MAX_ROWS = 10000;
 constexpr int SC_W = 64;  // window columns of a score tile
 // compaction: threads per workgroup, windows per thread, windows per workgroup
 constexpr int CP_THREADS = 256;
@@ -194,6 +201,11 @@ hipError_t launch_features_single(const LevelItem& it, int features, float clip,
                                   hipStream_t s);
 hipError_t launch_features_table(const LevelItem* items, const Tile* tiles, int n_tiles,
                                  int features, float clip, float eps, const Tuning& tu, hipStream_t s);
+// The form for few strips (same bits): block rows per workgroup for strips of
+// `width` lanes, and its launch.
+int feat_rows_chunk(int features, int width);
+hipError_t launch_features_rows_table(const LevelItem* items, const Tile* tiles, int n_tiles, int features,
+                                      float clip, float eps, hipStream_t s);
 // Fused HOG + LBP + pruner cell map (it.cmap), HOG|LBP only.
 hipError_t launch_features_cellmap_single(const LevelItem& it, float clip, float eps, hipStream_t s);
 hipError_t launch_features_cellmap_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip,
