@@ -31,6 +31,7 @@
 // an A fragment from LDS and a quarter of a B fragment from L2.
 #include <type_traits>
 
+#include "packed.h"
 #include "pd_internal.h"
 
 namespace pd {
@@ -42,11 +43,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int MF_COLS = 64;                       // window columns per tile
 constexpr int MF_ROWS = 4;                        // window rows per tile (one per wave)
-constexpr int MF_HOG_C = PD_HOG_BLOCK;            // 36 channels per block
-constexpr int MF_LBP_C = 60;                      // 59 bins + 1 zero
-constexpr int MF_HOG_T = 8;                       // K chunks of 32 per offset: 7*36 = 252 -> 256
-constexpr int MF_HOG_P = PD_WIN_BLOCKS_Y + 1;     // HOG weight slices: offset pairs (a, a + 1), a = -1 .. 14
-constexpr int MF_LBP_T = 15;                      // 8*60 = 480
 constexpr int MF_HOG_SR = MF_COLS + PD_WIN_BLOCKS_X - 1;  // 70 staged blocks per row
 constexpr int MF_LBP_SR = MF_COLS + PD_WIN_CELLS_X - 1;   // 71 staged cells per row
 constexpr int MF_HOG_ROW = MF_HOG_SR * MF_HOG_C + 8;      // bf16 per staged row (+ zero tail)
@@ -59,49 +55,6 @@ union MfmaShared {
     __bf16 ring[2][MF_ROW_MAX];
     f32x4 red[4][4][MF_ROWS][64];
 };
-
-__device__ __forceinline__ uint16_t f2bf(float f) { return f32_to_bf16(f); }
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-// ---- weight packing --------------------------------------------------------
-// HOG: [p 16][t 8][n 16][32]; LBP: [a 16][t 15][n 16][32] bf16; K index
-// k = 32 t + kk maps to (b, c) = (k / C, k % C) of the offset row.  LBP:
-// column n < 8 is the hi part of model n, n >= 8 the lo part of model n - 8.
-// HOG features are BF16, and the HOG weights carry their BF16 part only, so
-// a HOG slice holds two offsets: p = a + 1 for the pair (a, a + 1), column
-// n < 8 model n at offset a, n >= 8 model n - 8 at offset a + 1 (zero outside
-// 0 .. 14): one MFMA then serves two window rows.
-__global__ void pack_weights_kernel(const float* __restrict__ w, int n_models, uint16_t* __restrict__ out) {
-    const int hog_n = MF_HOG_P * MF_HOG_T * 16 * 32;
-    const int lbp_n = PD_WIN_CELLS_Y * MF_LBP_T * 16 * 32;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= hog_n + lbp_n) return;
-    const bool is_hog = e < hog_n;
-    const int q = is_hog ? e : e - hog_n;
-    const int T = is_hog ? MF_HOG_T : MF_LBP_T;
-    const int kk = q & 31;
-    const int n = (q >> 5) & 15;
-    const int t = (q >> 9) % T;
-    const int a = (q >> 9) / T;
-    const int k = 32 * t + kk;
-    const int m = n & 7;
-    float v = 0.0f;
-    if (m < n_models) {
-        if (is_hog) {
-            const int b = k / MF_HOG_C, c = k % MF_HOG_C;
-            const int off = n < 8 ? a - 1 : a;  // a is the slice index p here
-            if (b < PD_WIN_BLOCKS_X && off >= 0 && off < PD_WIN_BLOCKS_Y)
-                v = w[(size_t)m * PD_FEATURE_DIM + (off * PD_WIN_BLOCKS_X + b) * PD_HOG_BLOCK + c];
-        } else {
-            const int b = k / MF_LBP_C, c = k % MF_LBP_C;
-            if (b < PD_WIN_CELLS_X && c < PD_LBP_BINS)
-                v = w[(size_t)m * PD_FEATURE_DIM + PD_HOG_DIM + (a * PD_WIN_CELLS_X + b) * PD_LBP_BINS + c];
-        }
-    }
-    const uint16_t hi = f2bf(v);
-    // LBP counts are exact, so LBP weights carry hi + lo
-    out[e] = (is_hog || n < 8) ? hi : f2bf(v - bf2f(hi));
-}
 
 // ---- scoring -----------------------------------------------------------------
 // Feature row y (clamped) of the tile, channel-innermost in LDS: the loads
@@ -423,16 +376,6 @@ __global__ void __launch_bounds__(256) mfma_table_kernel(const LevelItem* __rest
 }
 
 }  // namespace
-
-int64_t packed_weight_elems() {
-    return (int64_t)(MF_HOG_P * MF_HOG_T + PD_WIN_CELLS_Y * MF_LBP_T) * 16 * 32;
-}
-
-hipError_t launch_pack_weights(const float* w, int n_models, uint16_t* out, hipStream_t s) {
-    const int n = (int)packed_weight_elems();
-    pack_weights_kernel<<<ceil_div(n, 256), 256, 0, s>>>(w, n_models, out);
-    return hipGetLastError();
-}
 
 hipError_t launch_mfma_single(const LevelItem& it, const uint16_t* wpk, const float* bias, int n_models, int features,
                               hipStream_t s) {

@@ -6,14 +6,15 @@
 //   windows with score > threshold are appended to their frame's candidate
 //   list with an atomic counter.  A frame's list has room for every one of
 //   its windows, so none is dropped.
-// select: for a frame with more than PD_MAX_CANDIDATES candidates, the
+// select (in the NMS kernel): for a frame with more than PD_MAX_CANDIDATES candidates, the
 //   PD_MAX_CANDIDATES highest-scoring ones (score descending, then level, i,
 //   j ascending: a strict order, keys are distinct) by a radix select over
 //   the 64-bit NMS sort key; the selected set does not depend on the order
 //   in which compaction appended the list.
 // nms: one workgroup (16 waves) per frame.  Candidates are sorted by (score descending,
-//   level, i, j ascending) with a bitonic sort in LDS; the greedy pass walks
-//   them in chunks of 64: a candidate is suppressed if it overlaps (IoU > 0.5,
+//   level, i, j ascending) in LDS, by counting up to 512 of them, else
+//   bitonically; their boxes are taken 1024 at a time, a thread each; the greedy
+//   pass walks them in chunks of 64: a candidate is suppressed if it overlaps (IoU > 0.5,
 //   decided exactly as 2*inter > union on integer boxes) a box kept in an
 //   earlier chunk (tested in parallel; per-candidate flags, no atomics) or an
 //   earlier kept box of its own chunk (a 64x64 overlap mask, one row per lane,
@@ -23,11 +24,6 @@
 
 namespace pd {
 namespace {
-
-__global__ void zero_kernel(int32_t* p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
 
 __global__ void __launch_bounds__(CP_THREADS) compact_kernel(const LevelItem* __restrict__ items,
                                                              const Tile* __restrict__ tiles, int n_models,
@@ -101,15 +97,16 @@ __global__ void __launch_bounds__(CP_THREADS) compact_kernel(const LevelItem* __
 // latency-bound, so the workgroup brings its own waves to hide the latency.
 constexpr int NMS_WAVES = 16;
 constexpr int NMS_THREADS = NMS_WAVES * 64;
+constexpr int NMS_COUNT = 512;  // longest list sorted by counting
 
 struct NmsSmem {
     unsigned long long key[PD_MAX_CANDIDATES];
     uint16_t sidx[PD_MAX_CANDIDATES];
     uint16_t kpos[PD_MAX_CANDIDATES];
     int4 kbox[PD_MAX_CANDIDATES];
-    int4 cbox[64];
+    int4 cbox[NMS_THREADS];  // boxes of the candidates in work (NMS_THREADS at a time)
     unsigned long long cmask[64];  // in-chunk overlap bits: candidate q's later overlaps
-    uint32_t supf[64];  // candidate of the chunk overlaps an earlier kept box (every writer stores 1)
+    uint32_t supf[NMS_COUNT];  // candidate of the chunk overlaps an earlier kept box (every writer stores 1; 64 used)
     int nkept;
 };
 
@@ -124,13 +121,19 @@ __device__ inline unsigned long long sort_key(float s, int4 k) {
 
 __device__ inline int4 window_box(const NmsGeom& g, int level, int i, int j) {
     level = min(max(level, 0), g.n_levels - 1);
-    const int64_t w0 = g.wh[0][0], h0 = g.wh[0][1];
-    const int64_t wk = g.wh[level][0], hk = g.wh[level][1];
+    // floor(256 p n0 / nk) in double: both sides of the division are integers
+    // below 2^37, so a quotient that is no integer lies at least 1 / nk > 2^-15
+    // from one, far more than the division's rounding; the integer division it
+    // stands for takes about five times the instructions
+    auto q8 = [](int p, int n0, int nk) {
+        return (int)((256.0 * (double)p) * (double)n0 / (double)nk);
+    };
+    const int w0 = g.wh[0][0], h0 = g.wh[0][1], wk = g.wh[level][0], hk = g.wh[level][1];
     int4 b;
-    b.x = (int)((256LL * PD_CELL * j * w0) / wk);
-    b.y = (int)((256LL * PD_CELL * i * h0) / hk);
-    b.z = (int)((256LL * (PD_CELL * j + PD_WIN_W) * w0) / wk);
-    b.w = (int)((256LL * (PD_CELL * i + PD_WIN_H) * h0) / hk);
+    b.x = q8(PD_CELL * j, w0, wk);
+    b.y = q8(PD_CELL * i, h0, hk);
+    b.z = q8(PD_CELL * j + PD_WIN_W, w0, wk);
+    b.w = q8(PD_CELL * i + PD_WIN_H, h0, hk);
     return b;
 }
 
@@ -145,68 +148,48 @@ __device__ inline bool overlaps(const int4& a, const int4& b) {
     return 2.0 * inter > uni;
 }
 
-// One workgroup per frame.  Finds the PD_MAX_CANDIDATES-th smallest key of
-// the frame's list, one byte per pass from the top (LDS histogram of the
-// keys that share the bytes found so far), then copies every entry whose key
-// is at most that one: exactly PD_MAX_CANDIDATES entries, the keys being
-// distinct.  Their order in the output is immaterial (NMS sorts by key).
-constexpr int SEL_THREADS = 1024;
-
-__global__ void __launch_bounds__(SEL_THREADS) cand_select_kernel(const NmsGeom* __restrict__ geoms,
-                                                                  const int32_t* __restrict__ counters,
-                                                                  const float* __restrict__ cand_score,
-                                                                  const int4* __restrict__ cand_key,
-                                                                  const double* __restrict__ cand_s64,
-                                                                  float* __restrict__ sel_score,
-                                                                  int4* __restrict__ sel_key,
-                                                                  double* __restrict__ sel_s64) {
-    const int f = blockIdx.x, t = threadIdx.x;
-    const int n = min(counters[f], geoms[f].cand_cap);
-    if (n <= PD_MAX_CANDIDATES) return;
-    const size_t base = (size_t)geoms[f].cand_off;
-    const float* cs = cand_score + base;
-    const int4* ck = cand_key + base;
+// Finds the PD_MAX_CANDIDATES-th smallest key of the frame's list, one byte per
+// pass from the top (LDS histogram of the keys that share the bytes found so
+// far), then copies every entry whose key is at most that one: exactly
+// PD_MAX_CANDIDATES entries, the keys being distinct.  Their order in the
+// output is immaterial (NMS sorts by key).  The whole workgroup.
+__device__ void select_candidates(int n, const float* __restrict__ cs, const int4* __restrict__ ck,
+                                  const double* __restrict__ c64, float* __restrict__ sel_score,
+                                  int4* __restrict__ sel_key, double* __restrict__ sel_s64) {
+    const int t = threadIdx.x;
     __shared__ uint32_t hist[256];
-    __shared__ unsigned long long s_prefix;
-    __shared__ int s_rank, s_out;
+    __shared__ uint32_t found[2];
+    __shared__ int s_out;
     unsigned long long prefix = 0ull, mask = 0ull;
-    int rank = PD_MAX_CANDIDATES;  // 1-based rank sought among the keys matching prefix
+    uint32_t rank = PD_MAX_CANDIDATES;  // 1-based rank sought among the keys matching prefix
     for (int shift = 56; shift >= 0; shift -= 8) {
         if (t < 256) hist[t] = 0u;
         __syncthreads();
-        for (int q = t; q < n; q += SEL_THREADS) {
+        for (int q = t; q < n; q += NMS_THREADS) {
             const unsigned long long key = sort_key(cs[q], ck[q]);
             if ((key & mask) == prefix) atomicAdd(&hist[(uint32_t)(key >> shift) & 255u], 1u);
         }
         __syncthreads();
-        if (t == 0) {
-            int acc = 0, d = 0;
-            for (; d < 255; ++d) {
-                if (acc + (int)hist[d] >= rank) break;
-                acc += (int)hist[d];
-            }
-            s_rank = rank - acc;
-            s_prefix = prefix | ((unsigned long long)d << shift);
-        }
+        if (t < 64) select_bin<true>(hist, rank, found);
         __syncthreads();
-        rank = s_rank;
-        prefix = s_prefix;
+        rank = found[1];
+        prefix |= (unsigned long long)found[0] << shift;
         mask |= 255ull << shift;
-        __syncthreads();  // s_rank / s_prefix are rewritten by the next pass
+        __syncthreads();  // found is rewritten by the next pass
     }
     if (t == 0) s_out = 0;
     __syncthreads();
-    const size_t o = (size_t)f * PD_MAX_CANDIDATES;
-    for (int q = t; q < n; q += SEL_THREADS) {
+    for (int q = t; q < n; q += NMS_THREADS) {
         if (sort_key(cs[q], ck[q]) <= prefix) {
             const int pos = atomicAdd(&s_out, 1);
             if (pos < PD_MAX_CANDIDATES) {
-                sel_score[o + pos] = cs[q];
-                sel_key[o + pos] = ck[q];
-                if (sel_s64) sel_s64[o + pos] = cand_s64[base + q];
+                sel_score[pos] = cs[q];
+                sel_key[pos] = ck[q];
+                if (sel_s64) sel_s64[pos] = c64[q];
             }
         }
     }
+    __syncthreads();
 }
 
 __device__ void nms_frame(const NmsGeom& g, int frame, int raw_count, const float* __restrict__ cs,
@@ -224,6 +207,28 @@ __device__ void nms_frame(const NmsGeom& g, int frame, int raw_count, const floa
     }
     if (t == 0) sm.nkept = 0;
     __syncthreads();
+    if (n <= NMS_COUNT) {
+        // a short list is sorted by counting: a candidate's place is the number
+        // of smaller keys (keys are distinct; equal ones, which only callers of
+        // pd_nms could give, keep their order), NMS_THREADS / np2 threads of one
+        // wave pass counting a run of the keys each.  Two barriers, where the
+        // bitonic sort takes 36 for 256 candidates.
+        const int per = NMS_THREADS / np2, run = (n + per - 1) / per;
+        const int q = t % np2, first = t / np2 * run;
+        uint32_t* const place = sm.supf;  // NMS_COUNT words from supf on: cleared first
+        for (int e = t; e < np2; e += NMS_THREADS) place[e] = 0u;
+        __syncthreads();
+        if (q < n) {
+            const unsigned long long mine = sm.key[q];
+            uint32_t less = 0;
+            for (int e = first; e < min(first + run, n); ++e)
+                less += (sm.key[e] < mine || (sm.key[e] == mine && e < q)) ? 1u : 0u;
+            if (less) atomicAdd(&place[q], less);
+        }
+        __syncthreads();
+        if (t < n) sm.sidx[place[t]] = (uint16_t)t;
+        __syncthreads();
+    } else
     for (int k = 2; k <= np2; k <<= 1) {
         for (int jj = k >> 1; jj > 0; jj >>= 1) {
             for (int q = t; q < np2; q += NMS_THREADS) {
@@ -246,10 +251,11 @@ __device__ void nms_frame(const NmsGeom& g, int frame, int raw_count, const floa
 
     for (int c0 = 0; c0 < n; c0 += 64) {
         const int cn = min(64, n - c0);
-        if (t < cn) {
+        if ((c0 & (NMS_THREADS - 1)) == 0 && c0 + t < n) {  // the next chunks' boxes, a thread each
             const int4 k = ck[sm.sidx[c0 + t]];
             sm.cbox[t] = window_box(g, k.x, k.y, k.z);
         }
+        const int4* const cbox = sm.cbox + (c0 & (NMS_THREADS - 1));
         if (t < 64) {
             sm.supf[t] = 0u;
             sm.cmask[t] = 0ull;
@@ -261,7 +267,7 @@ __device__ void nms_frame(const NmsGeom& g, int frame, int raw_count, const floa
             // against the boxes kept in earlier chunks: lane q of every wave
             // takes candidate q, the NMS_WAVES waves split the kept list, two
             // boxes per step
-            const int4 cb = sm.cbox[q];
+            const int4 cb = cbox[q];
             bool hit = false;
             for (int kk = part; kk < K && !hit; kk += 2 * NMS_WAVES) {
                 const int k2 = min(kk + NMS_WAVES, K - 1);
@@ -275,7 +281,7 @@ __device__ void nms_frame(const NmsGeom& g, int frame, int raw_count, const floa
 #pragma unroll
             for (int u = 0; u < 64 / NMS_WAVES; ++u) {
                 const int r = (64 / NMS_WAVES) * part + u;
-                if (r > q && r < cn && overlaps(cb, sm.cbox[r])) m |= 1ull << r;
+                if (r > q && r < cn && overlaps(cb, cbox[r])) m |= 1ull << r;
             }
             if (m) atomicOr(&sm.cmask[q], m);
         }
@@ -303,7 +309,7 @@ __device__ void nms_frame(const NmsGeom& g, int frame, int raw_count, const floa
             }
             if ((alive >> q) & 1ull) {
                 const int at = K + __popcll(alive & ((1ull << q) - 1ull));
-                sm.kbox[at] = sm.cbox[q];
+                sm.kbox[at] = cbox[q];
                 sm.kpos[at] = (uint16_t)(c0 + q);
             }
             if (q == 0) sm.nkept = K + __popcll(alive);
@@ -346,27 +352,26 @@ __global__ void __launch_bounds__(NMS_THREADS) nms_table_kernel(const NmsGeom* _
                                                         const float* __restrict__ cand_score,
                                                         const int4* __restrict__ cand_key,
                                                         const double* __restrict__ cand_s64,
-                                                        const float* __restrict__ sel_score,
-                                                        const int4* __restrict__ sel_key,
-                                                        const double* __restrict__ sel_s64,
+                                                        float* __restrict__ sel_score, int4* __restrict__ sel_key,
+                                                        double* __restrict__ sel_s64,
                                                         const int32_t* __restrict__ near_count,
                                                         pd_box* __restrict__ boxes, int cap,
                                                         pd_counts* __restrict__ counts) {
     const int f = blockIdx.x;
     const int n = counters[f];
-    const float* cs;
-    const int4* ck;
-    const double* c64;
-    if (n > PD_MAX_CANDIDATES) {  // the selected highest-scoring candidates
-        const size_t o = (size_t)f * PD_MAX_CANDIDATES;
-        cs = sel_score + o;
-        ck = sel_key + o;
-        c64 = sel_s64 ? sel_s64 + o : nullptr;
-    } else {
-        const size_t o = (size_t)geoms[f].cand_off;
-        cs = cand_score + o;
-        ck = cand_key + o;
-        c64 = cand_s64 ? cand_s64 + o : nullptr;
+    const size_t o = (size_t)geoms[f].cand_off;
+    const float* cs = cand_score + o;
+    const int4* ck = cand_key + o;
+    const double* c64 = cand_s64 ? cand_s64 + o : nullptr;
+    if (n > PD_MAX_CANDIDATES) {  // the highest-scoring candidates, in the frame's slot of the sel_* arrays
+        const size_t so = (size_t)f * PD_MAX_CANDIDATES;
+        float* const ss = sel_score + so;
+        int4* const sk = sel_key + so;
+        double* const s64 = sel_s64 ? sel_s64 + so : nullptr;
+        select_candidates(min(n, geoms[f].cand_cap), cs, ck, c64, ss, sk, s64);
+        cs = ss;
+        ck = sk;
+        c64 = s64;
     }
     nms_frame(geoms[f], f, n, cs, ck, c64, near_count ? near_count[f] : 0, boxes, cap, counts);
 }
@@ -382,12 +387,6 @@ static_assert(kNmsSmem <= 160 * 1024, "NMS scratch exceeds LDS");
 
 }  // namespace
 
-hipError_t launch_zero_i32(int32_t* p, int n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    zero_kernel<<<ceil_div(n, 256), 256, 0, s>>>(p, n);
-    return hipGetLastError();
-}
-
 hipError_t launch_compact(const LevelItem* items, const Tile* tiles, int n_tiles, int n_models,
                           const double* thresholds, float margin, int32_t* counters, float* cand_score,
                           int4* cand_key, double* cand_s64, int32_t* near_count, int4* near_key, int64_t near_cap,
@@ -398,18 +397,9 @@ hipError_t launch_compact(const LevelItem* items, const Tile* tiles, int n_tiles
     return hipGetLastError();
 }
 
-hipError_t launch_cand_select(const NmsGeom* geoms, int n_frames, const int32_t* counters, const float* cand_score,
-                              const int4* cand_key, const double* cand_s64, float* sel_score, int4* sel_key,
-                              double* sel_s64, hipStream_t s) {
-    if (n_frames <= 0) return hipSuccess;
-    cand_select_kernel<<<n_frames, SEL_THREADS, 0, s>>>(geoms, counters, cand_score, cand_key, cand_s64, sel_score,
-                                                        sel_key, sel_s64);
-    return hipGetLastError();
-}
-
 hipError_t launch_nms_table(const NmsGeom* geoms, int n_frames, const int32_t* counters,
                             const float* cand_score, const int4* cand_key, const double* cand_s64,
-                            const float* sel_score, const int4* sel_key, const double* sel_s64,
+                            float* sel_score, int4* sel_key, double* sel_s64,
                             const int32_t* near_count, pd_box* boxes, int cap, pd_counts* counts, hipStream_t s) {
     if (n_frames <= 0) return hipSuccess;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&nms_table_kernel),

@@ -713,10 +713,6 @@ int enqueue_decide(const DetectRun& R, const DetectLayout& L, const float* weigh
                                                     thresholds, R.counters, R.cscore, R.ckey, R.c64, R.orient, s),
                                    "rescore")))
         return rc;
-    if ((rc = hip_status(launch_cand_select(R.geoms, n_frames, R.counters, R.cscore, R.ckey, R.c64, R.sel_score,
-                                            R.sel_key, R.sel_64, s),
-                         "candidate select")))
-        return rc;
     marks.mark(PD_STAGE_NMS, s);
     return hip_status(launch_nms_table(R.geoms, n_frames, R.counters, R.cscore, R.ckey, R.c64, R.sel_score, R.sel_key,
                                        R.sel_64, L.bf16 ? R.near_count : nullptr, boxes, cap, counts, s),
@@ -740,18 +736,23 @@ int enqueue_detect(const DetectRun& R, const DetectLayout& L, const Tuning& tu, 
                    pd_box* boxes, int cap, pd_counts* counts, StageMarks& marks, hipStream_t s) {
     int rc;
     marks.mark(PD_STAGE_ZERO, s);
-    if ((rc = hip_status(launch_zero_i32(R.counters, R.n_zero, s), "zero"))) return rc;
-    if (!L.bf16 && !R.s32_pairs && (rc = hip_status(launch_pack_score32(weights, n_models, R.s32_pack, s), "pack")))
-        return rc;
-    if (L.bf16) {
-        if ((rc = hip_status(launch_orient_table(R.orient, s), "gradient table"))) return rc;
-        if ((rc = hip_status(launch_pack_weights(weights, n_models, R.packed, s), "pack"))) return rc;
-        if ((rc = hip_status(launch_pack_rowgemm(weights, R.packed + packed_weight_elems(), s), "pack"))) return rc;
+    Prep prep;
+    prep.weights = weights;
+    prep.n_models = n_models;
+    if (!L.bf16) {
+        if (!R.s32_pairs) prep.s32 = R.s32_pack;
+    } else {
+        if (L.rowgemm) prep.rowgemm = R.packed + packed_weight_elems();
+        else prep.mfma = R.packed;
+        prep.orient = R.orient;
     }
-    if (L.prune && (rc = hip_status(launch_pruner_pack_bf16(params->pruner, R.prpack, s), "pruner pack")))
-        return rc;
+    if (L.prune) {
+        prep.pruner = params->pruner;
+        prep.layers = R.prpack;
+    }
+    if ((rc = hip_status(launch_prep(prep, s), "prep"))) return rc;
     marks.mark(PD_STAGE_RESIZE, s);
-    if ((rc = hip_status(launch_resize_table(R.items, R.t_rs, R.nrs, s), "resize"))) return rc;
+    if ((rc = hip_status(launch_resize_table(R.items, R.t_rs, R.nrs, R.counters, R.n_zero, s), "resize"))) return rc;
     marks.mark(PD_STAGE_FEATURES, s);
     if (L.prune) {
         if ((rc = hip_status(launch_features_cellmap_table(R.items, R.t_ft, R.nft, params->clip, params->eps, tu, s),
@@ -1108,7 +1109,10 @@ int pd_pruner_logits_bf16(const uint8_t* lvl, int w, int h, int pitch, const pd_
     int rc;
     if ((rc = stage_upload(host.data(), host.size(), ws, s))) return rc;
     uint16_t* packed = reinterpret_cast<uint16_t*>(ws + L.off_packed);
-    if ((rc = hip_status(launch_pruner_pack_bf16(pruner, packed, s), "pruner pack"))) return rc;
+    Prep prep;
+    prep.pruner = pruner;
+    prep.layers = packed;
+    if ((rc = hip_status(launch_prep(prep, s), "pruner pack"))) return rc;
     if ((rc = hip_status(launch_features_cellmap_single(it, params->clip, params->eps, s), "cell map"))) return rc;
     return hip_status(launch_pruner_mfma(reinterpret_cast<const LevelItem*>(ws + L.off_item),
                                          reinterpret_cast<const Tile*>(ws + L.off_tiles), L.n_tiles, pruner, packed,
@@ -1214,10 +1218,12 @@ int pd_pack_models(const float* weights, int n_models, uint16_t* packed, void* s
     if (n_models < 1 || n_models > PD_MAX_MODELS_BF16)
         return fail(PD_E_SIZE, "n_models %d outside [1, %d]", n_models, PD_MAX_MODELS_BF16);
     if (!weights || !packed) return fail(PD_E_ARG, "NULL pointer argument");
-    if (int rc = hip_status(launch_pack_weights(weights, n_models, packed, (hipStream_t)stream), "pack launch"))
-        return rc;
-    return hip_status(launch_pack_rowgemm(weights, packed + packed_weight_elems(), (hipStream_t)stream),
-                      "pack launch");
+    Prep prep;
+    prep.weights = weights;
+    prep.n_models = n_models;
+    prep.mfma = packed;
+    prep.rowgemm = packed + packed_weight_elems();
+    return hip_status(launch_prep(prep, (hipStream_t)stream), "pack launch");
 }
 
 int pd_score_windows_bf16(const uint16_t* blocks_bf16, const uint8_t* cells, int cells_x, int cells_y,

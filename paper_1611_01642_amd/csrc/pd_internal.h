@@ -157,6 +157,33 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t planes_rsrc(const void* base, 
                                              0x00020000);
 }
 
+// One wave: the bin of hist[256] that holds the rank-th (1-based) entry counted
+// from bin 0 (ASCENDING) or from bin 255, and the entry's rank within the bin,
+// into out[0], out[1] (bin 255 or 0 where there are fewer entries).
+template <bool ASCENDING>
+__device__ __forceinline__ void select_bin(const uint32_t* hist, uint32_t rank, uint32_t* out) {
+    const int lane = threadIdx.x & 63;
+    uint32_t c[4], mine = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        c[k] = hist[ASCENDING ? 4 * lane + k : 255 - (4 * lane + k)];
+        mine += c[k];
+    }
+    uint32_t upto = mine;  // entries in the bins of lanes 0 .. lane
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t v = __shfl_up(upto, d, 64);
+        if (lane >= d) upto += v;
+    }
+    const uint64_t reached = __ballot(upto >= rank);
+    if (lane != (reached ? __builtin_ctzll(reached) : 63)) return;
+    uint32_t left = rank - (upto - mine);
+    int k = 0;
+    while (k < 3 && c[k] < left) left -= c[k++];
+    out[0] = (uint32_t)(ASCENDING ? 4 * lane + k : 255 - (4 * lane + k));
+    out[1] = left;
+}
+
 // FP32 -> BF16, round to nearest even (finite inputs).
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     uint32_t u = __float_as_uint(f);
@@ -191,9 +218,24 @@ struct Tuning {
     int grid = 0;            // 0: one workgroup per tile group; > 0: at most this many, looping
 };
 
+// What a call packs before use (prep.hip): the parts whose destination is given.
+struct Prep {
+    const float* weights = nullptr;  // SVM models
+    int n_models = 0;
+    float* s32 = nullptr;            // FP32 scoring, score32_packed_floats(n_models)
+    uint16_t* rowgemm = nullptr;     // BF16, one model, rowgemm_packed_elems()
+    uint16_t* mfma = nullptr;        // BF16, up to 8 models, packed_weight_elems()
+    const float* pruner = nullptr;   // the pruner's parameters
+    uint16_t* layers = nullptr;      // its BF16 fragments, pruner_packed_bf16_elems()
+    double2* orient = nullptr;       // the FP64 rescore's gradient table, ORIENT_BYTES
+};
+
 // ---- launchers (each defined next to its kernel) ---------------------------
+hipError_t launch_prep(const Prep& p, hipStream_t s);
 hipError_t launch_resize_single(const LevelItem* items, int n_items, hipStream_t s);
-hipError_t launch_resize_table(const LevelItem* items, const Tile* tiles, int n_tiles, hipStream_t s);
+// Also clears `zero` (n_zero ints): the counters of the launches that follow.
+hipError_t launch_resize_table(const LevelItem* items, const Tile* tiles, int n_tiles, int32_t* zero, int n_zero,
+                               hipStream_t s);
 
 hipError_t launch_lbp_codes(const uint8_t* img, int w, int h, int pitch, uint8_t* codes,
                             int codes_pitch, hipStream_t s);
@@ -229,7 +271,6 @@ int64_t score32_band_capacity(int nx, int ny, int wc);
 // caller's own weights.
 int score32_wave_tiles(const LevelItem* items, int n_items, Tile* out);
 int score32_wave_pairs(int64_t n_entries);
-hipError_t launch_pack_score32(const float* w, int n_models, float* out, hipStream_t s);
 // Threshold decisions taken as the FP32 scores are stored (one model, no
 // keep set): windows above their frame's threshold are appended to the
 // frame's candidate list as compaction appends them.  counters NULL: none.
@@ -260,13 +301,11 @@ hipError_t launch_fold_lbp_weights(const float* wb, int n_models, float* w, hipS
 
 int64_t packed_weight_elems();
 int64_t rowgemm_packed_elems();
-hipError_t launch_pack_rowgemm(const float* w, uint16_t* out, hipStream_t s);
 hipError_t launch_rowgemm_single(const LevelItem& it, const uint16_t* packed, const float* bias, hipStream_t s);
 hipError_t launch_rowgemm_table(const LevelItem* items, const Tile* tiles, int n_tiles, const uint16_t* packed,
                                 const float* bias, int grid, hipStream_t s);
 // row-GEMM scoring (one model): tile = 64 window columns, all rows
 constexpr int RG_TILE_C = 64;
-hipError_t launch_pack_weights(const float* w, int n_models, uint16_t* out, hipStream_t s);
 hipError_t launch_mfma_single(const LevelItem& it, const uint16_t* wpk, const float* bias, int n_models, int features,
                               hipStream_t s);
 hipError_t launch_mfma_table(const LevelItem* items, const Tile* tiles, int n_tiles, const uint16_t* wpk,
@@ -286,7 +325,6 @@ hipError_t launch_compact(const LevelItem* items, const Tile* tiles, int n_tiles
 // 0..255, dx in -255..255) holds (orientation bin coordinate, magnitude).
 constexpr int ORIENT_W = 511, ORIENT_H = 256;
 constexpr int64_t ORIENT_BYTES = (int64_t)ORIENT_W * ORIENT_H * 16;
-hipError_t launch_orient_table(double2* table, hipStream_t s);
 // features: PD_FEAT_HOG | PD_FEAT_LBP subset; the dot products run over
 // that family's features only (the other family's weights are not read).
 hipError_t launch_rescore64(const LevelItem* items, const int32_t* frame_first_item, int n_frames,
@@ -294,25 +332,19 @@ hipError_t launch_rescore64(const LevelItem* items, const int32_t* frame_first_i
                             const float* bias, int n_models, int features, float clip, float eps,
                             const double* thresholds, int32_t* counters, float* cand_score, int4* cand_key,
                             double* cand_s64, const double2* orient, hipStream_t s);
-// Per frame whose candidate list is longer than PD_MAX_CANDIDATES: the
-// PD_MAX_CANDIDATES entries with the smallest NMS sort keys (score
-// descending, then level, i, j ascending) copied to the frame's slot of the
-// sel_* arrays ([n_frames][PD_MAX_CANDIDATES]).  Other frames are left alone.
-hipError_t launch_cand_select(const NmsGeom* geoms, int n_frames, const int32_t* counters, const float* cand_score,
-                              const int4* cand_key, const double* cand_s64, float* sel_score, int4* sel_key,
-                              double* sel_s64, hipStream_t s);
-// NMS per frame over its candidate list, or over its sel_* slot when the
-// list is longer than PD_MAX_CANDIDATES.
+// NMS per frame over its candidate list.  Of a list longer than
+// PD_MAX_CANDIDATES it takes the PD_MAX_CANDIDATES entries with the smallest
+// sort keys (score descending, then level, i, j ascending), through the frame's
+// slot of the sel_* arrays ([n_frames][PD_MAX_CANDIDATES]).
 hipError_t launch_nms_table(const NmsGeom* geoms, int n_frames, const int32_t* counters,
                             const float* cand_score, const int4* cand_key, const double* cand_s64,
-                            const float* sel_score, const int4* sel_key, const double* sel_s64,
-                            const int32_t* near_count, pd_box* boxes, int cap, pd_counts* counts, hipStream_t s);
+                            float* sel_score, int4* sel_key, double* sel_s64, const int32_t* near_count, pd_box* boxes, int cap,
+                            pd_counts* counts, hipStream_t s);
 hipError_t launch_nms_single(const NmsGeom& g, int n, const float* cand_score, const int4* cand_key,
                              pd_box* boxes, int cap, pd_counts* counts, hipStream_t s);
 // BF16 MFMA inference of the pruner network (channels-last BF16 maps).
 constexpr int PR_CP1 = 72;  // layer-1 input channel stride
 int64_t pruner_packed_bf16_elems();
-hipError_t launch_pruner_pack_bf16(const float* params, uint16_t* packed, hipStream_t s);
 int pruner_mfma_tiles_y(int hc);  // row pairs
 // Per frame, the K-th largest window logit (-inf when K >= windows).
 hipError_t launch_topk(const LevelItem* items, const int32_t* first_item, const NmsGeom* geoms, int n_frames,
@@ -335,8 +367,6 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n, int 
                        float eps, hipStream_t s);
 hipError_t launch_window_labels(const float* scores, int nx, int ny, int wc, int hc, const double* thr,
                                 float* labels, float* mask, hipStream_t s);
-
-hipError_t launch_zero_i32(int32_t* p, int n, hipStream_t s);
 
 // The paper's own mappings, as ablation baselines (baselines.hip).
 hipError_t launch_lbp_naive(const uint8_t* codes, int pitch, int wc, int hc, uint32_t* hist, hipStream_t s);

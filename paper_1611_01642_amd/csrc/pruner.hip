@@ -33,6 +33,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "packed.h"
 #include "pd_internal.h"
 
 namespace pd {
@@ -504,43 +505,9 @@ __global__ void __launch_bounds__(256) window_labels_kernel(const float* __restr
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-template <int L>
-struct Layer;
-template <>
-struct Layer<1> {
-    static constexpr int CIN = 68, CP = PR_CP1, XS = PR_CP1, COUT = 32;
-};
-template <>
-struct Layer<2> {
-    static constexpr int CIN = 32, CP = 32, XS = 40, COUT = 32;
-};
-template <>
-struct Layer<3> {
-    static constexpr int CIN = 32, CP = 32, XS = 40, COUT = 16;
-};
-template <int L>
-struct LayerDims : Layer<L> {
-    static constexpr int KCH = (9 * Layer<L>::CP + 31) / 32;  // K chunks of 32
-    static constexpr int NT = Layer<L>::COUT / 16;            // N tiles
-    static constexpr int PACKED = KCH * NT * 64 * 8;          // bf16 values
-    static constexpr int PARAMS = Layer<L>::COUT * Layer<L>::CIN * 9;
-};
-
 constexpr int MR = 2;           // output rows per workgroup
 constexpr int MC = 64;          // output cells per row
 constexpr int XR = MR + 2, XC = MC + 2;
-
-template <int L>
-__global__ void __launch_bounds__(256) pack_bf16_kernel(const float* __restrict__ w, uint16_t* __restrict__ out) {
-    using D = LayerDims<L>;
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= D::PACKED) return;
-    const int t = e / (D::NT * 512), n = (e / 512) % D::NT, l = (e / 8) % 64, j = e % 8;
-    const int k = 32 * t + 8 * (l >> 4) + j, och = 16 * n + (l & 15);
-    const int tap = k / D::CP, c = k - tap * D::CP;
-    const float v = (tap < 9 && c < D::CIN) ? w[((size_t)och * D::CIN + c) * 9 + tap] : 0.0f;
-    out[e] = f32_to_bf16(v);
-}
 
 template <int L>
 __global__ void __launch_bounds__(256) conv_mfma_kernel(const LevelItem* __restrict__ items,
@@ -754,21 +721,6 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n, int 
 hipError_t launch_window_labels(const float* scores, int nx, int ny, int wc, int hc, const double* thr,
                                 float* labels, float* mask, hipStream_t s) {
     window_labels_kernel<<<ceil_div(wc * hc, 256), 256, 0, s>>>(scores, nx, ny, wc, hc, thr, labels, mask);
-    return hipGetLastError();
-}
-
-int64_t pruner_packed_bf16_elems() {
-    return (int64_t)LayerDims<1>::PACKED + LayerDims<2>::PACKED + LayerDims<3>::PACKED;
-}
-
-hipError_t launch_pruner_pack_bf16(const float* params, uint16_t* packed, hipStream_t s) {
-    const float* w1 = params;
-    const float* w2 = w1 + LayerDims<1>::PARAMS + 32;
-    const float* w3 = w2 + LayerDims<2>::PARAMS + 32;
-    pack_bf16_kernel<1><<<ceil_div(LayerDims<1>::PACKED, 256), 256, 0, s>>>(w1, packed);
-    pack_bf16_kernel<2><<<ceil_div(LayerDims<2>::PACKED, 256), 256, 0, s>>>(w2, packed + LayerDims<1>::PACKED);
-    pack_bf16_kernel<3><<<ceil_div(LayerDims<3>::PACKED, 256), 256, 0, s>>>(
-        w3, packed + LayerDims<1>::PACKED + LayerDims<2>::PACKED);
     return hipGetLastError();
 }
 

@@ -166,23 +166,6 @@ __device__ __forceinline__ void dot_models4(RescoreShared& sm, const float4* __r
     }
 }
 
-// The gradient table: for dy in 0..255 and dx in -255..255, the
-// orientation's bin coordinate t = angle / 20 - 0.5 in [-0.5, 8.5) (angle in
-// degrees, folded into [0, 180): Algorithm 4 with the device's double atan2)
-// and the magnitude sqrt(dx^2 + dy^2), both FP64.  A gradient with dy < 0
-// looks up (-dx, -dy): the same magnitude and, mathematically, the same
-// folded angle (its FP64 value may differ in the last bits).
-__global__ void orient_table_kernel(double2* __restrict__ table) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= ORIENT_W * ORIENT_H) return;
-    const int dy = e / ORIENT_W, dx = e - dy * ORIENT_W - 255;
-    const double mag = sqrt((double)(dx * dx + dy * dy));
-    double ang = atan2((double)dy, (double)dx) * 57.295779513082320876798154814105;
-    if (ang < 0.0) ang += 180.0;
-    if (ang >= 180.0) ang -= 180.0;
-    table[e] = make_double2(ang / 20.0 - 0.5, mag);
-}
-
 // Bilinear weight of pixel offset p in [0, 8) of a cell towards cell d in {-1, 0, 1}.
 __device__ __forceinline__ double spatial_w(int p, int d) {
     const double w = 1.0 - fabs((double)p + 0.5 - (8.0 * d + 4.0)) / 8.0;
@@ -449,11 +432,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) r
 }
 
 }  // namespace
-
-hipError_t launch_orient_table(double2* table, hipStream_t s) {
-    orient_table_kernel<<<ceil_div(ORIENT_W * ORIENT_H, 256), 256, 0, s>>>(table);
-    return hipGetLastError();
-}
 
 hipError_t launch_rescore64(const LevelItem* items, const int32_t* frame_first_item, int n_frames,
                             const int32_t* near_count, const int4* near_key, const float* weights, const float* bias,

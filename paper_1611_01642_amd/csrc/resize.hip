@@ -219,7 +219,10 @@ __global__ void __launch_bounds__(256) resize_single_kernel(ResizeArgs a) {
 // run of the table instead, so the levels of a frame, which all read the same
 // source image, mostly share one XCD's L2.
 __global__ void __launch_bounds__(256) resize_table_kernel(const LevelItem* __restrict__ items,
-                                                           const Tile* __restrict__ tiles, int n_tiles) {
+                                                           const Tile* __restrict__ tiles, int n_tiles,
+                                                           int32_t* __restrict__ zero, int n_zero) {
+    // the call's counters, cleared here (a launch of their own would cost 4 us)
+    for (int e = (int)blockIdx.x * 256 + threadIdx.x; e < n_zero; e += (int)gridDim.x * 256) zero[e] = 0;
     const int run = (n_tiles + N_XCD - 1) / N_XCD;
     const int t = (int)(blockIdx.x % N_XCD) * run + (int)(blockIdx.x / N_XCD);
     if (t >= n_tiles) return;
@@ -255,9 +258,10 @@ hipError_t launch_resize_single(const LevelItem* items, int n_items, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_resize_table(const LevelItem* items, const Tile* tiles, int n_tiles, hipStream_t s) {
-    if (n_tiles <= 0) return hipSuccess;
-    resize_table_kernel<<<N_XCD * ((n_tiles + N_XCD - 1) / N_XCD), 256, 0, s>>>(items, tiles, n_tiles);
+hipError_t launch_resize_table(const LevelItem* items, const Tile* tiles, int n_tiles, int32_t* zero, int n_zero,
+                               hipStream_t s) {
+    const int grid = N_XCD * ((n_tiles + N_XCD - 1) / N_XCD);
+    resize_table_kernel<<<grid > 0 ? grid : 1, 256, 0, s>>>(items, tiles, n_tiles, zero, n_zero);
     return hipGetLastError();
 }
 

@@ -22,6 +22,7 @@
 // ahead, so they are in flight during two rows of MFMAs.
 #include <type_traits>
 
+#include "packed.h"
 #include "pd_internal.h"
 
 namespace pd {
@@ -32,19 +33,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int RG_COLS = 64;
-constexpr int RG_HOG_T = 8;    // K chunks of 32 per HOG row: 7 * 36 = 252 -> 256
-constexpr int RG_LBP_T = 15;   // 8 * 60 = 480 (59 bins padded to 60)
-constexpr int RG_HOG_C = PD_HOG_BLOCK;
-constexpr int RG_LBP_C = 60;
 constexpr int RG_HOG_SR = RG_COLS + PD_WIN_BLOCKS_X - 1;  // 70 staged blocks
 constexpr int RG_LBP_SR = RG_COLS + PD_WIN_CELLS_X - 1;   // 71 staged cells
 constexpr int RG_HOG_ROW = (RG_HOG_SR * RG_HOG_C + 8 + 7) / 8 * 8;
 constexpr int RG_LBP_ROW = (RG_LBP_SR * RG_LBP_C + 8 + 7) / 8 * 8;
-
-// packed B fragments: [HOG hi: t 8][LBP hi: t 15][LBP lo: t 15], each
-// [lane 64][8] bf16 (lane: column a = lane % 16, K group lane / 16)
-constexpr int RG_FRAG = 64 * 8;
-constexpr int RG_PACKED = (RG_HOG_T + 2 * RG_LBP_T) * RG_FRAG;
 
 struct RowShared {
     __bf16 hog[2][RG_HOG_ROW];
@@ -52,29 +44,6 @@ struct RowShared {
     __bf16 blbp[RG_LBP_T * RG_FRAG];  // the LBP weights' lo fragments
     float ring[4][16][16];  // per wave: window-row slot x window column
 };
-
-__global__ void pack_rowgemm_kernel(const float* __restrict__ w, uint16_t* __restrict__ out) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= RG_PACKED) return;
-    const int f = e / RG_FRAG, r = e - f * RG_FRAG;
-    const int lane = r >> 3, kk = r & 7;
-    const int a = lane & 15;
-    float v = 0.0f;
-    bool lo = false;
-    if (f < RG_HOG_T) {
-        const int k = 32 * f + 8 * (lane >> 4) + kk;
-        const int b = k / RG_HOG_C, c = k % RG_HOG_C;
-        if (a < PD_WIN_BLOCKS_Y && b < PD_WIN_BLOCKS_X) v = w[(a * PD_WIN_BLOCKS_X + b) * PD_HOG_BLOCK + c];
-    } else {
-        const int t = (f - RG_HOG_T) % RG_LBP_T;
-        lo = f >= RG_HOG_T + RG_LBP_T;
-        const int k = 32 * t + 8 * (lane >> 4) + kk;
-        const int b = k / RG_LBP_C, c = k % RG_LBP_C;
-        if (b < PD_WIN_CELLS_X && c < PD_LBP_BINS) v = w[PD_HOG_DIM + (a * PD_WIN_CELLS_X + b) * PD_LBP_BINS + c];
-    }
-    const uint16_t hi = f32_to_bf16(v);
-    out[e] = lo ? f32_to_bf16(v - __uint_as_float((uint32_t)hi << 16)) : hi;
-}
 
 template <bool HOG>
 struct RowRegs {
@@ -321,13 +290,6 @@ __global__ void __launch_bounds__(256) rowgemm_table_kernel(const LevelItem* __r
 }
 
 }  // namespace
-
-int64_t rowgemm_packed_elems() { return RG_PACKED; }
-
-hipError_t launch_pack_rowgemm(const float* w, uint16_t* out, hipStream_t s) {
-    pack_rowgemm_kernel<<<ceil_div(RG_PACKED, 256), 256, 0, s>>>(w, out);
-    return hipGetLastError();
-}
 
 hipError_t launch_rowgemm_single(const LevelItem& it, const uint16_t* packed, const float* bias, hipStream_t s) {
     if (it.nx <= 0 || it.ny <= 0) return hipSuccess;

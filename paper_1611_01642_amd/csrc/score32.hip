@@ -51,6 +51,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "packed.h"
 #include "pd_internal.h"
 
 namespace pd {
@@ -58,20 +59,6 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int S32_HOG_T = PD_HOG_BLOCK / 4;             // 9 chunks of 4 channels
-constexpr int S32_LBP_T = (PD_LBP_BINS + 3) / 4;         // 15: channel 59 has zero weight
-constexpr int S32_HOG_K = PD_WIN_BLOCKS_Y + 1;           // 16 feature rows per pair
-constexpr int S32_LBP_K = PD_WIN_CELLS_Y + 1;            // 17
-// Weight row a of the model (HOG 0 .. 14, LBP 0 .. 15) holds [t][b 8][c 4]
-// floats, plus 2: the s = 1 lanes then read 2 banks away from the s = 0 ones.
-// One zero row follows: the B fragments of rows a' - s outside the model
-// read it.
-constexpr int S32_HOG_RS = S32_HOG_T * 32 + 2;
-constexpr int S32_LBP_RS = S32_LBP_T * 32 + 2;
-constexpr int S32_HOG_N = PD_WIN_BLOCKS_Y * S32_HOG_RS;
-constexpr int S32_LBP_N = PD_WIN_CELLS_Y * S32_LBP_RS;
-constexpr int S32_ZERO = S32_HOG_N + S32_LBP_N;  // the zero row (S32_LBP_RS floats)
-constexpr int S32_MODEL = (S32_ZERO + S32_LBP_RS + 3) / 4 * 4;  // floats per packed model (50 KB)
 constexpr int S32_SUBS = 4;                              // sub-tiles per tile
 constexpr int S32_WAVES = 2 * S32_SUBS;                  // waves per workgroup: sub-tile x pair parity
 constexpr int S32_OS = 17;                               // row stride of a staged 16 x 16 O tile
@@ -89,29 +76,6 @@ constexpr int S32_PIECES = S32_PIECES_H + PD_LBP_BINS;     // + 59 LBP
 constexpr int S32_PPT = (S32_PIECES + 63) / 64;            // pieces per lane (4)
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// ---- weight packing --------------------------------------------------------
-// Model m's floats at m * S32_MODEL: HOG rows a = 0 .. 14, then LBP rows
-// a = 0 .. 15, then the zero row; element (a, t, b, k) = W[a][b][4 t + k]
-// (zero for HOG b = 7 and LBP channel 59).
-__global__ void pack32_kernel(const float* __restrict__ w, int n_models, float* __restrict__ out) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_models * S32_MODEL) return;
-    const int m = e / S32_MODEL, q = e - m * S32_MODEL;
-    const float* wm = w + (size_t)m * PD_FEATURE_DIM;
-    float v = 0.0f;
-    if (q < S32_HOG_N) {
-        const int a = q / S32_HOG_RS, x = q - a * S32_HOG_RS;
-        const int t = x >> 5, b = (x >> 2) & 7, c = 4 * t + (x & 3);
-        if (x < S32_HOG_T * 32 && b < PD_WIN_BLOCKS_X) v = wm[(a * PD_WIN_BLOCKS_X + b) * PD_HOG_BLOCK + c];
-    } else if (q < S32_ZERO) {
-        const int q2 = q - S32_HOG_N;
-        const int a = q2 / S32_LBP_RS, x = q2 - a * S32_LBP_RS;
-        const int t = x >> 5, b = (x >> 2) & 7, c = 4 * t + (x & 3);
-        if (x < S32_LBP_T * 32 && c < PD_LBP_BINS) v = wm[PD_HOG_DIM + (a * PD_WIN_CELLS_X + b) * PD_LBP_BINS + c];
-    }
-    out[e] = v;
-}
 
 // ---- scoring -----------------------------------------------------------------
 // Band table entry (Tile): item, ty = the band's first window row (even),
@@ -750,8 +714,6 @@ void launch_feat(int rows, dim3 grid, const LevelItem* items, const Tile* bands,
 
 }  // namespace
 
-int64_t score32_packed_floats(int n_models) { return (int64_t)n_models * S32_MODEL; }
-
 // Bands of 4 x `rows` window rows (`rows` = 4, 8 or 16 per wave) over runs
 // of 16-column tiles, for every level of the table, as 8 lists, one per XCD,
 // each longest first.  With 16 frames or more each frame's bands go to one
@@ -862,12 +824,6 @@ int score32_wave_pairs(int64_t n_entries) {
 int64_t score32_band_capacity(int nx, int ny, int wc) {
     if (nx <= 0 || ny <= 0) return 0;
     return (int64_t)ceil_div(ny, 2 * s32_pairs(4)) * ceil_div(ceil_div(wc, S32_TILE), 2);
-}
-
-hipError_t launch_pack_score32(const float* w, int n_models, float* out, hipStream_t s) {
-    const int n = n_models * S32_MODEL;
-    pack32_kernel<<<ceil_div(n, 256), 256, 0, s>>>(w, n_models, out);
-    return hipGetLastError();
 }
 
 hipError_t launch_score32_table(const LevelItem* items, const Tile* bands, const XcdLists& xs, int grid,
