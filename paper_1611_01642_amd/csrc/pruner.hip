@@ -750,70 +750,75 @@ __device__ __forceinline__ uint32_t fkey(float z) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// One workgroup per frame: radix selection (8 bits per pass, most significant
-// first) of the K-th largest logit over the frame's windows, every level.
-constexpr int TOPK_BATCH = 8;
+// One workgroup of 16 waves per frame: radix selection (8 bits per pass, most
+// significant first) of the K-th largest logit over the frame's windows, every
+// level.  The logits are read from memory once, their keys kept in LDS (frames
+// of more than TOPK_KEYS windows read them again in each pass); one wave finds
+// a pass's bin.  (4 waves that read the logits in every pass, with one thread
+// walking the bins, took 116 us for 16 frames of 1242x375; this takes 23.)
+constexpr int TOPK_THREADS = 1024;
+constexpr int TOPK_BATCH = 4;
+constexpr int TOPK_KEYS = 36 * 1024;
 
-__global__ void __launch_bounds__(256) topk_kernel(const LevelItem* __restrict__ items,
-                                                   const int32_t* __restrict__ first_item,
-                                                   const NmsGeom* __restrict__ geoms, int keep_k,
-                                                   float* __restrict__ kth) {
+__global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const LevelItem* __restrict__ items,
+                                                            const int32_t* __restrict__ first_item,
+                                                            const NmsGeom* __restrict__ geoms, int keep_k,
+                                                            float* __restrict__ kth) {
     __shared__ uint32_t hist[256];
-    __shared__ uint32_t sel[2];  // prefix, remaining rank
-    __shared__ int total_s;
+    __shared__ uint32_t found[2];
+    __shared__ uint32_t keys[TOPK_KEYS];
     const int f = blockIdx.x, tid = threadIdx.x;
-    const int i0 = first_item[f], nl = geoms[f].n_levels;
-    if (tid == 0) {
-        int n = 0;
-        for (int l = 0; l < nl; ++l) n += items[i0 + l].nx * items[i0 + l].ny;
-        total_s = n;
-        sel[0] = 0u;
-        sel[1] = (uint32_t)keep_k;
-    }
-    __syncthreads();
-    if (keep_k >= total_s) {  // every window is kept
+    const int i0 = first_item[f], nl = geoms[f].n_levels, total = geoms[f].cand_cap;
+    if (keep_k >= total) {  // every window is kept
         if (tid == 0) kth[f] = -INFINITY;
         return;
     }
-    uint32_t mask = 0u;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[tid] = 0u;
-        __syncthreads();
-        const uint32_t prefix = sel[0];
+    const bool held = total <= TOPK_KEYS;
+    // f(key, place) of every window, four loads of a thread in flight together
+    auto each = [&](auto&& visit) __attribute__((always_inline)) {
+        int base = 0;
         for (int l = 0; l < nl; ++l) {
             const LevelItem& it = items[i0 + l];
-            const int n = it.nx * it.ny;
-            // eight logit loads of a thread in flight together
-            for (int q0 = tid; q0 < n; q0 += 256 * TOPK_BATCH) {
+            const int n = it.nx * it.ny, nx = it.nx, wc = it.wc;
+            const float* const z = it.logit + PRUNER_WIN_DI * wc + PRUNER_WIN_DJ;
+            for (int q0 = tid; q0 < n; q0 += TOPK_THREADS * TOPK_BATCH) {
                 uint32_t k[TOPK_BATCH];
 #pragma unroll
                 for (int u = 0; u < TOPK_BATCH; ++u) {
-                    const int q = min(q0 + 256 * u, n - 1);
-                    const int wi = q / it.nx, wj = q - wi * it.nx;
-                    k[u] = fkey(it.logit[(size_t)(wi + PRUNER_WIN_DI) * it.wc + wj + PRUNER_WIN_DJ]);
+                    const int q = min(q0 + TOPK_THREADS * u, n - 1), wi = q / nx;
+                    k[u] = fkey(z[(size_t)wi * wc + (q - wi * nx)]);
                 }
 #pragma unroll
                 for (int u = 0; u < TOPK_BATCH; ++u)
-                    if (q0 + 256 * u < n && (k[u] & mask) == prefix) atomicAdd(&hist[(k[u] >> shift) & 255u], 1u);
+                    if (q0 + TOPK_THREADS * u < n) visit(k[u], base + q0 + TOPK_THREADS * u);
             }
+            base += n;
+        }
+    };
+    uint32_t mask = 0u, prefix = 0u, rank = (uint32_t)keep_k;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        if (tid < 256) hist[tid] = 0u;
+        __syncthreads();
+        auto count = [&](uint32_t k) {
+            if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
+        };
+        if (held && shift < 24) {
+            for (int q = tid; q < total; q += TOPK_THREADS) count(keys[q]);
+        } else {
+            each([&](uint32_t k, int q) {
+                if (held) keys[q] = k;
+                count(k);
+            });
         }
         __syncthreads();
-        if (tid == 0) {
-            uint32_t rank = sel[1], d = 255u;
-            for (;; --d) {
-                if (hist[d] >= rank || d == 0u) break;
-                rank -= hist[d];
-            }
-            sel[0] = prefix | (d << shift);
-            sel[1] = rank;
-        }
+        if (tid < 64) select_bin<false>(hist, rank, found);
+        __syncthreads();
+        prefix |= found[0] << shift;
+        rank = found[1];
         mask |= 255u << shift;
-        __syncthreads();
+        __syncthreads();  // found is rewritten by the next pass
     }
-    if (tid == 0) {
-        const uint32_t k = sel[0];
-        kth[f] = __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
-    }
+    if (tid == 0) kth[f] = __uint_as_float((prefix & 0x80000000u) ? (prefix & 0x7fffffffu) : ~prefix);
 }
 
 // One wave per score tile: does any of its windows have logit >= kth?
@@ -848,7 +853,7 @@ __global__ void __launch_bounds__(256) tile_filter_kernel(const LevelItem* __res
 hipError_t launch_topk(const LevelItem* items, const int32_t* first_item, const NmsGeom* geoms, int n_frames,
                        int keep_k, float* kth, hipStream_t s) {
     if (n_frames <= 0) return hipSuccess;
-    topk_kernel<<<n_frames, 256, 0, s>>>(items, first_item, geoms, keep_k, kth);
+    topk_kernel<<<n_frames, TOPK_THREADS, 0, s>>>(items, first_item, geoms, keep_k, kth);
     return hipGetLastError();
 }
 

@@ -1,8 +1,10 @@
 """NMS at the lengths where its sort and its batches of boxes change form, on
-the largest frame side's boxes too: exact."""
+the largest frame side's boxes too, and the pruner's top-K over frames with
+more windows than its LDS keeps: exact."""
 import numpy as np
 import pytest
 
+import pd_synth
 from oracle import pd_oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -39,3 +41,28 @@ def test_nms_lengths(n, wh):
     assert cnt["candidates"] == n and cnt["kept"] == len(exp) and cnt["overflow"] == 0
     assert [(int(b["level"]), int(b["i"]), int(b["j"])) for b in got] == [(c["level"], c["i"], c["j"]) for c in exp]
     assert [tuple(int(b[k]) for k in ("x0", "y0", "x1", "y1")) for b in got] == [c["box"] for c in exp]
+
+
+# 120,936 windows (read again in each pass) and 3 (all in one)
+@pytest.mark.parametrize("w,h,keeps", [(1920, 1080, (1, 1000, 100000)), (80, 136, (1, 2, 3))])
+def test_top_k(w, h, keeps):
+    """With every window above the threshold, the pruned detector's candidates are the windows whose logit reaches the
+    K-th largest: K of them, ties aside."""
+    frame = torch.from_numpy(pd_synth.frame(w, h, 9)).to(DEV)
+    weights, bias = torch.from_numpy(pd_synth.svm_weights(1)).to(DEV), torch.zeros(1, device=DEV)
+    pruner = torch.from_numpy(pd_synth.pruner_init(seed=2)).to(DEV)
+    thr = torch.full((1,), -1e30, dtype=torch.float64, device=DEV)
+    sizes = [(L.w, L.h) for L in pd.plan_pyramid(w, h, pd.params())[0]]
+    views = pd.build_pyramid(frame)[2]
+    logits = []
+    for (lw, lh), v in zip(sizes, views):
+        z = pd.pruner_logits_bf16(v, pruner)
+        ny, nx = O.window_grid(lw, lh)
+        logits.append(z[7:7 + ny, 3:3 + nx].flatten())
+    z = torch.cat(logits).cpu().numpy()
+    for keep in keeps:
+        det = pd.Detector([frame], weights, bias, pd.params(prune_keep=keep, pruner=pruner), cap=16)
+        det.run(thr)
+        torch.cuda.synchronize()
+        n = int(det.counts.cpu().numpy().view(pd.COUNTS_DTYPE)[0]["candidates"])
+        assert n == int((z >= np.sort(z)[::-1][keep - 1]).sum())
