@@ -41,6 +41,8 @@
 namespace pd {
 namespace {
 
+typedef uint32_t __attribute__((aligned(1))) u32_any;
+
 constexpr int RS_PY = PD_WIN_H + 2;  // 130 pixel rows incl. halo
 constexpr int RS_PX = PD_WIN_W + 2;  // 66 pixel columns incl. halo
 constexpr int RS_CELLS = PD_WIN_CELLS_Y * PD_WIN_CELLS_X;  // 128
@@ -199,12 +201,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) r
         int tt = t;
         asm volatile("" : "+v"(tt));
         // pixels of the window + one halo pixel: every load of a thread in
-        // flight together, then the LDS stores.  A window whose halo lies
-        // inside the level reads aligned words (its rows start 1 byte before
-        // an 8-byte boundary of a 4-byte aligned row; the last word holds the
-        // halo column, so no word leaves the row); others read bytes,
-        // clamped to the level.
-        const bool inner = wi > 0 && wj > 0 && PD_CELL * wi + PD_WIN_H < it.h && PD_CELL * wj + PD_WIN_W < it.w;
+        // flight together, then the LDS stores.  A window whose halo, and the
+        // three pixels after it, lie inside the level reads words (at any
+        // alignment: level 0 is the caller's frame), so that no word leaves the
+        // row; others read bytes, clamped to the level.
+        const bool inner = wi > 0 && wj > 0 && PD_CELL * wi + PD_WIN_H < it.h && PD_CELL * wj + PD_WIN_W + 4 <= it.w;
         if (inner) {
             const auto base = it.pyr + (size_t)(PD_CELL * wi - 1) * it.pitch + (PD_CELL * wj - 4);
             uint32_t v[RS_PXW_PER_T];
@@ -212,7 +213,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) r
             for (int k = 0; k < RS_PXW_PER_T; ++k) {
                 const int e = min(tt + 256 * k, RS_PY * RS_ROW_WORDS - 1);
                 const int r = e / RS_ROW_WORDS, d = e - r * RS_ROW_WORDS;
-                v[k] = *reinterpret_cast<const uint32_t*>(base + (size_t)r * it.pitch + 4 * d);
+                v[k] = *reinterpret_cast<const u32_any*>(base + (size_t)r * it.pitch + 4 * d);
             }
 #pragma unroll
             for (int k = 0; k < RS_PXW_PER_T; ++k) {
