@@ -552,6 +552,7 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
     for (size_t k = 0; k < L.sizes.size(); k += 2)
         strip_rows += (int64_t)feat_tiles_x(L.sizes[k] / PD_CELL) * (L.sizes[k + 1] / PD_CELL);
     R.feat_rows = !L.prune && strip_rows <= FR_MAX_ROWS;
+    const int rs_rows = resize_rows(L.n_rs);
     for (int f = 0; f < n_frames; ++f) {
         geoms[f].n_levels = L.level_count[f];
         geoms[f].cand_off = L.cand_off[f];
@@ -581,10 +582,9 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
             it.cand_cap = L.cand_cap[f];
             geoms[f].wh[k][0] = it.w;
             geoms[f].wh[k][1] = it.h;
-            if (k > 0) {  // tiles of `rows` rows (at least RS_TY: within the capacity counted above)
-                const int rows = resize_rows(it.w, it.h, it.src_w, it.src_h);
-                for (int y = 0; y < it.h; y += rows)
-                    for (int tx = 0; tx < resize_tiles_x(it.w); ++tx) t_rs[nrs++] = Tile{q, y, tx, rows};
+            if (k > 0) {  // tiles of `rs_rows` rows (within the capacity counted above)
+                for (int y = 0; y < it.h; y += rs_rows)
+                    for (int tx = 0; tx < resize_tiles_x(it.w); ++tx) t_rs[nrs++] = Tile{q, y, tx, rs_rows};
             }
             const int fty = feat_tiles_y(it.hc, tu.feat_rows);
             if (L.prune) {

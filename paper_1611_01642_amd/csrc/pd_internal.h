@@ -77,11 +77,9 @@ struct NmsGeom {
 constexpr int N_XCD = 8;
 
 // ---- tile shapes ---------------------------------------------------------
-// resize: 64 lanes x 4 pixels wide, 16 rows
-constexpr int RS_TX = 256;      // pixels per tile row
-constexpr int RS_TY = 16;       // rows per tile (single-image launches; the least in tables)
-constexpr int RS_TY_MAX = 128;  // rows per tile in tables
-constexpr int RS_LDS = 20 * 1024;  // staged source bytes per resize workgroup (7 workgroups per CU)
+// resize: a tile is 64 lanes x 4 pixels wide, its rows split over 4 waves
+constexpr int RS_TX = 256;  // pixels per tile row
+constexpr int RS_TY = 16;   // rows per tile at least (the tables' capacity)
 // features: one wave = a strip of 64 cell columns (one per lane) walking
 // down FT_CH block rows (+1 overlap cell row); it owns 63 block columns
 constexpr int FT_W = 64;
@@ -193,17 +191,14 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 
 __host__ __device__ inline int resize_tiles_x(int w) { return ceil_div(w, RS_TX); }
 __host__ __device__ inline int resize_tiles_y(int h) { return ceil_div(h, RS_TY); }
-// Rows per resize tile of a w x h level sampled from a sw x sh image: as many
-// (a multiple of 4, RS_TY..RS_TY_MAX) as keep the tile's source rectangle
-// within the staging buffer, so that levels near full scale run few, tall tiles.
-inline int resize_rows(int w, int h, int sw, int sh) {
-    const double sx = (double)sw / w, sy = (double)sh / h;
-    const double row_bytes = (RS_TX - 1) * sx + 12.0;  // source span of a tile row + alignment slack
-    const double src_rows = RS_LDS / row_bytes - 3.0;
-    int rows = (int)(src_rows / sy) + 1;
-    rows = rows / 4 * 4;
-    return rows < RS_TY ? RS_TY : (rows > RS_TY_MAX ? RS_TY_MAX : rows);
-}
+// Rows per resize tile (16 per wave at most) of a call with `tiles` tiles of
+// RS_TY rows.  Taller tiles share more rows' horizontal passes and pay for
+// their set-up less often, shorter ones fill more of the chip (1024 workgroups
+// are four per CU).  us at 16 / 32 / 64 rows: one 1242x375 frame (700 tiles)
+// 7.8 / 9.2 / 13.0, 4 frames 13.7 / 13.0 / 14.9, 16 (11200 tiles) 30.9 / 29.9 /
+// 29.4, 64 frames 112.5 / 101.6 / 96.2, 256 421 / 376 / 362 (128 rows: 368),
+// all before the next row's loads had registers of their own (64: 354).
+inline int resize_rows(int64_t tiles) { return tiles <= 1024 ? RS_TY : tiles <= 8192 ? 2 * RS_TY : 4 * RS_TY; }
 __host__ __device__ inline int feat_tiles_x(int wc) { return wc <= 1 ? 1 : ceil_div(wc - 1, FT_BX); }
 // Strips that also emit the pruner cell map own 62 columns: every owned cell
 // needs both neighbours in the same wave.
