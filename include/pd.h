@@ -95,7 +95,8 @@ typedef struct pd_params {
                             (0.05)                                          */
     /* Tile and launch shapes of pd_detect (0 = default).  They change the
        work partition only, never a result; pd_autotune picks them.        */
-    int32_t tune_feat_rows;  /* block rows per feature strip: 4..32 (8)    */
+    int32_t tune_feat_rows;  /* block rows per feature strip: 4..32
+                                (0: chosen by the strips' number)          */
     int32_t tune_score_rows; /* PD_PREC_F32 window rows per scoring band:
                                 4, 8 or 16 (8)                             */
     int32_t tune_grid;       /* 0: default grids; n > 0: feature and

@@ -862,10 +862,10 @@ hipError_t feat_single(const LevelItem& it, float clip, float eps, hipStream_t s
 
 template <int FEAT>
 hipError_t feat_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip, float eps,
-                      const Tuning& tu, hipStream_t s) {
+                      int rows, int grid, hipStream_t s) {
     int blocks = ceil_div(n_tiles, FT_WAVES);
-    if (tu.grid > 0) blocks = min(blocks, tu.grid);
-    features_table_kernel<FEAT><<<blocks, FT_WAVES * 64, 0, s>>>(items, tiles, n_tiles, tu.feat_rows, clip, eps);
+    if (grid > 0) blocks = min(blocks, grid);
+    features_table_kernel<FEAT><<<blocks, FT_WAVES * 64, 0, s>>>(items, tiles, n_tiles, rows, clip, eps);
     return hipGetLastError();
 }
 
@@ -899,11 +899,11 @@ hipError_t launch_features_cellmap_single(const LevelItem& it, float clip, float
 }
 
 hipError_t launch_features_cellmap_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip,
-                                         float eps, const Tuning& tu, hipStream_t s) {
+                                         float eps, int rows, int grid, hipStream_t s) {
     if (n_tiles <= 0) return hipSuccess;
     int blocks = ceil_div(n_tiles, FT_WAVES);
-    if (tu.grid > 0) blocks = min(blocks, tu.grid);
-    cellmap_table_kernel<<<blocks, FT_WAVES * 64, 0, s>>>(items, tiles, n_tiles, tu.feat_rows, clip, eps);
+    if (grid > 0) blocks = min(blocks, grid);
+    cellmap_table_kernel<<<blocks, FT_WAVES * 64, 0, s>>>(items, tiles, n_tiles, rows, clip, eps);
     return hipGetLastError();
 }
 
@@ -925,13 +925,13 @@ hipError_t launch_features_single(const LevelItem& it, int features, float clip,
 }
 
 hipError_t launch_features_table(const LevelItem* items, const Tile* tiles, int n_tiles, int features,
-                                 float clip, float eps, const Tuning& tu, hipStream_t s) {
+                                 float clip, float eps, int rows, int grid, hipStream_t s) {
     if (n_tiles <= 0) return hipSuccess;
     switch (features & (PD_FEAT_HOG | PD_FEAT_LBP)) {
-        case PD_FEAT_HOG: return feat_table<PD_FEAT_HOG>(items, tiles, n_tiles, clip, eps, tu, s);
-        case PD_FEAT_LBP: return feat_table<PD_FEAT_LBP>(items, tiles, n_tiles, clip, eps, tu, s);
+        case PD_FEAT_HOG: return feat_table<PD_FEAT_HOG>(items, tiles, n_tiles, clip, eps, rows, grid, s);
+        case PD_FEAT_LBP: return feat_table<PD_FEAT_LBP>(items, tiles, n_tiles, clip, eps, rows, grid, s);
         case PD_FEAT_HOG | PD_FEAT_LBP:
-            return feat_table<PD_FEAT_HOG | PD_FEAT_LBP>(items, tiles, n_tiles, clip, eps, tu, s);
+            return feat_table<PD_FEAT_HOG | PD_FEAT_LBP>(items, tiles, n_tiles, clip, eps, rows, grid, s);
         default: return hipSuccess;
     }
 }

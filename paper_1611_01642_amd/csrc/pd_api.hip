@@ -6,6 +6,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <string>
 #include <vector>
 
@@ -504,6 +505,7 @@ struct DetectRun {
     XcdLists xs{};     // FP32 scoring: the band table's per-XCD lists
     int s32_grid = 0;  // and its launch width
     bool feat_rows = false;  // features with a wave per cell row (few strips)
+    int strip_rows = FT_CH;  // else: block rows per strip
     int s32_pairs = 0;  // FP32 scoring by the wave kernel: row pairs per wave (0: the band kernel)
     int32_t* s32_ctr = nullptr;
     float* s32_pack = nullptr;
@@ -530,6 +532,96 @@ struct DetectRun {
     uint16_t* prpack = nullptr;  // BF16 fragment-packed pruner weights
 };
 
+// Columns of a level's feature strips: `full` strips of 63 block columns, the
+// remaining ones in a narrower lane group of `width` lanes, whose waves take
+// 64 / width row chunks each.
+struct StripCols {
+    int full, width;
+    bool narrow;
+};
+
+StripCols strip_cols(int wc) {
+    const int wb = wc - 1;
+    const int full = wb > 0 ? wb / FT_BX : 0;
+    const int tail = wb > 0 ? wb - full * FT_BX : 0;
+    int width = 2;
+    while (width - 1 < std::max(tail, 1)) width *= 2;
+    return {full, width, tail > 0 || full == 0};
+}
+
+// Block rows per feature strip.  Two workgroups of four strips fit a CU, so a
+// call takes a few rounds of 512 workgroups, and the time of one that walks l
+// cell rows is close to l + 1: the rows (4 < R <= 16) whose workgroups,
+// longest first, end soonest, the least of equals.  Measured over R = 4..32 on
+// batches of 16..256 frames of 1242x375, 64 mixed ones and others, that is
+// within 3 % of the best R everywhere, where 8 for all loses up to 28 %: 16
+// frames 191 -> 149 us, 32 301 -> 257, 64 479 -> 485, 128 912 -> 888, 256
+// 1769 -> 1706.
+int strip_rows(const DetectLayout& L) {
+    struct Level {
+        int rows, full, tail, count;  // block rows; strips per chunk row; chunks per narrow strip; equal levels
+    };
+    std::vector<Level> levels;
+    size_t at = 0, last = 0, last_n = 0;  // levels of the frame before (equal frames are counted once)
+    for (const int n : L.level_count) {
+        const int* wh = &L.sizes[2 * at];
+        if (last_n && (int)last_n == n && n && std::equal(wh, wh + 2, &L.sizes[2 * (at - n)])) {
+            for (size_t k = 0; k < last_n; ++k) ++levels[last + k].count;
+        } else {
+            last = levels.size();
+            for (int k = 0; k < n; ++k) {
+                const int wc = wh[2 * k] / PD_CELL, hc = wh[2 * k + 1] / PD_CELL;
+                if (L.prune) {
+                    levels.push_back({hc - 1, feat_tiles_x_cm(wc), 0, 1});
+                } else {
+                    const StripCols c = strip_cols(wc);
+                    levels.push_back({hc - 1, c.full, c.narrow ? 64 / c.width : 0, 1});
+                }
+            }
+            last_n = n;
+        }
+        at += n;
+    }
+    constexpr int MAX_ROWS = 16, SLOTS = 512;
+    int best = FT_CH;
+    int64_t best_end = INT64_MAX;
+    for (int R = FT_MIN_ROWS + 1; R <= MAX_ROWS; ++R) {
+        int64_t strips[MAX_ROWS + 1] = {};  // by block rows
+        for (const Level& l : levels) {
+            const int chunks = std::max(ceil_div(l.rows, R), 1), rest = l.rows - (chunks - 1) * R;
+            strips[R] += (int64_t)l.count * l.full * (chunks - 1);
+            strips[std::max(rest, 0)] += (int64_t)l.count * l.full;
+            if (l.tail) {  // a narrow strip's wave is as long as its first chunk
+                const int waves = ceil_div(chunks, l.tail);
+                const bool alone = (waves - 1) * l.tail == chunks - 1;  // the last wave holds the last chunk only
+                strips[R] += (int64_t)l.count * (waves - (alone ? 1 : 0));
+                if (alone) strips[std::max(rest, 0)] += l.count;
+            }
+        }
+        // workgroups to the slot free first, equal ones together
+        std::map<int64_t, int64_t> slots{{0, SLOTS}};  // time free -> slots
+        int64_t seen = 0, end = 0;
+        for (int r = R; r >= 0; --r) {
+            int64_t n = (seen + strips[r] + 3) / 4 - (seen + 3) / 4;
+            seen += strips[r];
+            while (n > 0) {
+                const auto first = slots.begin();
+                const int64_t t = first->first + r + 2, m = std::min(n, first->second);
+                if (m == first->second) slots.erase(first);
+                else first->second -= m;
+                slots[t] += m;
+                end = std::max(end, t);
+                n -= m;
+            }
+        }
+        if (end < best_end) {
+            best = R;
+            best_end = end;
+        }
+    }
+    return best;
+}
+
 // Builds the level, tile and NMS tables of one call in host memory `stage`
 // (L.table_bytes), laid out as they are uploaded to device memory `tbl`: the
 // start of the workspace `ws` for pd_detect, a graph's own buffer for a
@@ -548,10 +640,11 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
     Tile* t_cp = t_sc + L.n_sc;
     Tile* t_pr = t_cp + L.n_cp;
     int q = 0, nrs = 0, nft = 0, nsc = 0, ncp = 0, npr = 0;
-    int64_t strip_rows = 0;
+    int64_t row_waves = 0;
     for (size_t k = 0; k < L.sizes.size(); k += 2)
-        strip_rows += (int64_t)feat_tiles_x(L.sizes[k] / PD_CELL) * (L.sizes[k + 1] / PD_CELL);
-    R.feat_rows = !L.prune && strip_rows <= FR_MAX_ROWS;
+        row_waves += (int64_t)feat_tiles_x(L.sizes[k] / PD_CELL) * (L.sizes[k + 1] / PD_CELL);
+    R.feat_rows = !L.prune && row_waves <= FR_MAX_ROWS;
+    if (!R.feat_rows) R.strip_rows = tu.feat_rows ? tu.feat_rows : strip_rows(L);
     const int rs_rows = resize_rows(L.n_rs);
     for (int f = 0; f < n_frames; ++f) {
         geoms[f].n_levels = L.level_count[f];
@@ -586,20 +679,14 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
                 for (int y = 0; y < it.h; y += rs_rows)
                     for (int tx = 0; tx < resize_tiles_x(it.w); ++tx) t_rs[nrs++] = Tile{q, y, tx, rs_rows};
             }
-            const int fty = feat_tiles_y(it.hc, tu.feat_rows);
+            const int fty = feat_tiles_y(it.hc, R.strip_rows);
             if (L.prune) {
                 for (int ty = 0; ty < fty; ++ty)
                     for (int tx = 0; tx < feat_tiles_x_cm(it.wc); ++tx) t_ft[nft++] = Tile{q, ty, tx, 0};
             } else {
-                // full 64-lane strips of 63 block columns; the remaining columns
-                // in narrower lane groups (pad = group width), each wave taking
-                // 64 / width row chunks
-                const int wb = it.wc - 1;
-                const int full = wb > 0 ? wb / FT_BX : 0;
-                const int tail = wb > 0 ? wb - full * FT_BX : 0;
-                int width = 2;
-                while (width - 1 < std::max(tail, 1)) width *= 2;
-                const bool narrow = tail > 0 || full == 0;
+                const StripCols c = strip_cols(it.wc);
+                const int full = c.full, width = c.width;
+                const bool narrow = c.narrow;
                 if (R.feat_rows) {  // entries of FR_SPAN workgroups
                     for (int tx = 0; tx < full + narrow; ++tx) {
                         const int wd = tx < full ? 64 : width;
@@ -634,7 +721,7 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
         // feature strips longest first (cell rows walked; with the cell map,
         // one more above all but the first), so that the launch ends on its
         // shortest strips: a counting sort, stable within a length
-        const int ch = tu.feat_rows;
+        const int ch = R.strip_rows;
         auto rows_of = [&](const Tile& t) {
             const int c0 = t.ty * ch;
             return std::max(0, std::min(c0 + ch, items[t.item].hc - 1) - c0 + 1);
@@ -755,7 +842,8 @@ int enqueue_detect(const DetectRun& R, const DetectLayout& L, const Tuning& tu, 
     if ((rc = hip_status(launch_resize_table(R.items, R.t_rs, R.nrs, R.counters, R.n_zero, s), "resize"))) return rc;
     marks.mark(PD_STAGE_FEATURES, s);
     if (L.prune) {
-        if ((rc = hip_status(launch_features_cellmap_table(R.items, R.t_ft, R.nft, params->clip, params->eps, tu, s),
+        if ((rc = hip_status(launch_features_cellmap_table(R.items, R.t_ft, R.nft, params->clip, params->eps, R.strip_rows,
+                                                                 tu.grid, s),
                              "features + cell map")))
             return rc;
         marks.mark(PD_STAGE_SCORE, s);
@@ -790,7 +878,7 @@ int enqueue_detect(const DetectRun& R, const DetectLayout& L, const Tuning& tu, 
     const hipError_t e = R.feat_rows ? launch_features_rows_table(R.items, R.t_ft, R.nft, params->features, params->clip,
                                                                   params->eps, s)
                                      : launch_features_table(R.items, R.t_ft, R.nft, params->features, params->clip,
-                                                             params->eps, tu, s);
+                                                             params->eps, R.strip_rows, tu.grid, s);
     if ((rc = hip_status(e, "features"))) return rc;
     marks.mark(PD_STAGE_SCORE, s);
     bool decided = false;
@@ -1475,7 +1563,7 @@ int pd_autotune(const pd_frame* frames, int n_frames, const float* weights, cons
     };
     pd_params cur = *params;
     const Tuning t0 = tuning_of(params);
-    cur.tune_feat_rows = t0.feat_rows;
+    cur.tune_feat_rows = t0.feat_rows ? t0.feat_rows : FT_CH;
     cur.tune_score_rows = t0.score_rows;
     float cur_ms = 0.0f;
     // one knob at a time (the stages they shape are independent)

@@ -89,10 +89,11 @@ constexpr int FT_WAVES = 4;  // waves (independent strips) per workgroup
 // features of few strips: a wave per cell row
 constexpr int FR_WAVES = 4;           // cell rows (of 64 lanes) per workgroup
 constexpr int FR_SPAN = 8;            // workgroups per table entry
-// strip rows (64 cells of one cell row) of a launch at most: about 14 pyramids
-// of 1242x375, where the two forms meet (8 frames: 100 us against 145 in
-// strips; 12: 137 and 148; 16: 180 and 194; 24: 259 and 201)
-constexpr int64_t FR_MAX_ROWS = 10000;
+// strip rows (64 cells of one cell row) of a launch at most: about 11 pyramids
+// of 1242x375, where the two forms meet (us here and in strips: 4 frames 56 and
+// 98, 8 frames 102 and 101, 10 frames 122 and 134, 12 frames 139 and 133, 16
+// frames 178 and 143; 2 frames of 1920x1080 116 and 133, 3 of them 162 and 135)
+constexpr int64_t FR_MAX_ROWS = 9000;
 constexpr int SC_W = 64;  // window columns of a score tile
 // compaction: threads per workgroup, windows per thread, windows per workgroup
 constexpr int CP_THREADS = 256;
@@ -208,7 +209,7 @@ __host__ __device__ inline int feat_tiles_y(int hc, int rows = FT_CH) { return h
 
 // Tile shapes and launch shapes chosen at run time (pd_params tuning fields).
 struct Tuning {
-    int feat_rows = FT_CH;   // block rows per feature strip (2..32)
+    int feat_rows = 0;       // block rows per feature strip (4..32; 0: by the strips, strip_rows)
     int score_rows = 8;      // FP32 scoring: window rows per band (4, 8 or 16)
     int grid = 0;            // 0: one workgroup per tile group; > 0: at most this many, looping
 };
@@ -237,7 +238,7 @@ hipError_t launch_lbp_codes(const uint8_t* img, int w, int h, int pitch, uint8_t
 hipError_t launch_features_single(const LevelItem& it, int features, float clip, float eps,
                                   hipStream_t s);
 hipError_t launch_features_table(const LevelItem* items, const Tile* tiles, int n_tiles,
-                                 int features, float clip, float eps, const Tuning& tu, hipStream_t s);
+                                 int features, float clip, float eps, int rows, int grid, hipStream_t s);
 // The form for few strips (same bits): block rows per workgroup for strips of
 // `width` lanes, and its launch.
 int feat_rows_chunk(int features, int width);
@@ -246,7 +247,7 @@ hipError_t launch_features_rows_table(const LevelItem* items, const Tile* tiles,
 // Fused HOG + LBP + pruner cell map (it.cmap), HOG|LBP only.
 hipError_t launch_features_cellmap_single(const LevelItem& it, float clip, float eps, hipStream_t s);
 hipError_t launch_features_cellmap_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip,
-                                         float eps, const Tuning& tu, hipStream_t s);
+                                         float eps, int rows, int grid, hipStream_t s);
 
 // FP32 scores of one image's windows (HOG and LBP), score32.hip.
 hipError_t launch_score_single(const LevelItem& it, const float* w, const float* bias, int n_models, hipStream_t s);
