@@ -71,11 +71,15 @@ constexpr int VOTE_SLOTS = 2 * 3 * VOTE_BINS;
 
 // What the previous cell row leaves for the next stays in registers, and the
 // workgroup's LDS (lookup table, byte counters, vote accumulators: 76 KB)
-// leaves room for two workgroups per CU.
+// leaves room for two workgroups per CU.  LBP alone has no accumulators (16 KB,
+// 7 workgroups by their registers): 128 frames of 1242x375 take 258 us, with
+// room for two workgroups they took 413.
+template <int FEAT, int WAVES = FT_WAVES>
 struct FeatShared {
-    uint32_t lut[256];                               // (increment << 7) | word
-    uint32_t cnt[FT_WAVES][FT_W * LBP_WORDS];        // lane-private byte counters
-    float vote[FT_WAVES][VOTE_SLOTS][FT_W];          // lane-private orientation votes
+    static constexpr int SLOTS = (FEAT & PD_FEAT_HOG) ? VOTE_SLOTS : 1;
+    uint32_t lut[256];                          // (increment << 7) | word
+    uint32_t cnt[WAVES][FT_W * LBP_WORDS];      // lane-private byte counters
+    float vote[WAVES][SLOTS][FT_W];             // lane-private orientation votes
 };
 
 // One pixel row of a cell's neighbourhood: byte i (0..9) is pixel x0 - 1 + i.
@@ -384,7 +388,7 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
                                                gptr<float> __restrict__ hog, gptr<uint16_t> __restrict__ hog16,
                                                gptr<uint8_t> __restrict__ lbp, gptr<float> __restrict__ cmap,
                                                gptr<uint16_t> __restrict__ cmap16, int ty, int tx, int ch, float clip,
-                                               float eps, FeatShared& sm, int wave, int group = 64) {
+                                               float eps, FeatShared<FEAT>& sm, int wave, int group = 64) {
     constexpr bool DO_HOG = (FEAT & PD_FEAT_HOG) != 0;
     constexpr bool DO_LBP = (FEAT & PD_FEAT_LBP) != 0;
     static_assert(!CM || (DO_HOG && DO_LBP), "the cell map needs HOG and LBP");
@@ -593,13 +597,6 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
 // bits.  A workgroup's first row is its neighbour's last one (with the cell
 // map, one more above), so it computes R rows for R - 1 block rows (R - 2), and
 // long launches keep the strips.
-template <int RW>
-struct RowShared {
-    uint32_t lut[256];
-    uint32_t cnt[RW][FT_W * LBP_WORDS];
-    float vote[RW][VOTE_SLOTS][FT_W];
-};
-
 // Block rows (cell rows without HOG) of a workgroup of R cell rows.
 template <int FEAT, bool CM>
 __host__ __device__ constexpr int row_chunk(int R) {
@@ -608,7 +605,7 @@ __host__ __device__ constexpr int row_chunk(int R) {
 
 template <int FEAT, bool CM, int RW>
 __device__ __forceinline__ void features_rows(const LevelItem& it, int cy0, int tx, int width, float clip, float eps,
-                                              RowShared<RW>& sm) {
+                                              FeatShared<FEAT, RW>& sm) {
     constexpr bool DO_HOG = (FEAT & PD_FEAT_HOG) != 0, DO_LBP = (FEAT & PD_FEAT_LBP) != 0;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = it.w, h = it.h, hc = it.hc, wc = it.wc, hb = hc - 1, wb = wc - 1;
@@ -753,7 +750,7 @@ __device__ inline void init_lut(uint32_t (&lut)[256]) {
 // One image: block x = strip, block y = chunk of rows.
 template <int FEAT, bool CM, int RW>
 __global__ void __launch_bounds__(RW * 64) features_rows_single_kernel(LevelItem it, float clip, float eps) {
-    __shared__ RowShared<RW> sm;
+    __shared__ FeatShared<FEAT, RW> sm;
     int width = 64;
     if (!CM) {
         const int left = max(it.wc - 1, 1) - (int)blockIdx.x * FT_BX;  // block columns from this strip on
@@ -771,7 +768,7 @@ template <int FEAT, int RW>
 __global__ void __launch_bounds__(RW * 64) features_rows_table_kernel(const LevelItem* __restrict__ items,
                                                                       const Tile* __restrict__ tiles, float clip,
                                                                       float eps) {
-    __shared__ RowShared<RW> sm;
+    __shared__ FeatShared<FEAT, RW> sm;
     const Tile tl = tiles[blockIdx.x];
     const LevelItem& it = items[tl.item];
     const int cy0 = tl.ty + blockIdx.y * row_chunk<FEAT, false>(RW * (64 / tl.pad));
@@ -783,7 +780,7 @@ __global__ void __launch_bounds__(RW * 64) features_rows_table_kernel(const Leve
 __global__ void __launch_bounds__(FT_WAVES * 64) cellmap_table_kernel(const LevelItem* __restrict__ items,
                                                             const Tile* __restrict__ tiles, int n_tiles, int ch,
                                                             float clip, float eps) {
-    __shared__ FeatShared sm;
+    __shared__ FeatShared<PD_FEAT_HOG | PD_FEAT_LBP> sm;
     init_lut<FT_WAVES * 64>(sm.lut);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int task = blockIdx.x * FT_WAVES + wave; task < n_tiles; task += gridDim.x * FT_WAVES) {
@@ -799,7 +796,7 @@ template <int FEAT>
 __global__ void __launch_bounds__(FT_WAVES * 64) features_table_kernel(const LevelItem* __restrict__ items,
                                                              const Tile* __restrict__ tiles, int n_tiles, int ch,
                                                              float clip, float eps) {
-    __shared__ FeatShared sm;
+    __shared__ FeatShared<FEAT> sm;
     init_lut<FT_WAVES * 64>(sm.lut);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // strips are independent per wave; a capped grid loops over them
@@ -814,7 +811,7 @@ __global__ void __launch_bounds__(FT_WAVES * 64) features_table_kernel(const Lev
 // One image in strips of FT_CH block rows (cell map: of cell rows).
 template <int FEAT, bool CM>
 __global__ void __launch_bounds__(FT_WAVES * 64) features_single_kernel(LevelItem it, float clip, float eps) {
-    __shared__ FeatShared sm;
+    __shared__ FeatShared<FEAT> sm;
     init_lut<FT_WAVES * 64>(sm.lut);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int task = blockIdx.x * FT_WAVES + wave;

@@ -549,15 +549,15 @@ StripCols strip_cols(int wc) {
     return {full, width, tail > 0 || full == 0};
 }
 
-// Block rows per feature strip.  Two workgroups of four strips fit a CU, so a
-// call takes a few rounds of 512 workgroups, and the time of one that walks l
+// Block rows per feature strip.  Two workgroups of four strips fit a CU (LBP
+// alone: 7), so a call takes a few rounds of 512 workgroups, and the time of one that walks l
 // cell rows is close to l + 1: the rows (4 < R <= 16) whose workgroups,
 // longest first, end soonest, the least of equals.  Measured over R = 4..32 on
 // batches of 16..256 frames of 1242x375, 64 mixed ones and others, that is
 // within 3 % of the best R everywhere, where 8 for all loses up to 28 %: 16
 // frames 191 -> 149 us, 32 301 -> 257, 64 479 -> 485, 128 912 -> 888, 256
-// 1769 -> 1706.
-int strip_rows(const DetectLayout& L) {
+// 1769 -> 1706 (LBP alone, 32 frames: 84 with the rows of 512, 65 with 1792's).
+int strip_rows(const DetectLayout& L, int features) {
     struct Level {
         int rows, full, tail, count;  // block rows; strips per chunk row; chunks per narrow strip; equal levels
     };
@@ -582,7 +582,8 @@ int strip_rows(const DetectLayout& L) {
         }
         at += n;
     }
-    constexpr int MAX_ROWS = 16, SLOTS = 512;
+    constexpr int MAX_ROWS = 16;
+    const int64_t n_slots = 256 * (features == PD_FEAT_LBP ? 7 : 2);
     int best = FT_CH;
     int64_t best_end = INT64_MAX;
     for (int R = FT_MIN_ROWS + 1; R <= MAX_ROWS; ++R) {
@@ -599,7 +600,7 @@ int strip_rows(const DetectLayout& L) {
             }
         }
         // workgroups to the slot free first, equal ones together
-        std::map<int64_t, int64_t> slots{{0, SLOTS}};  // time free -> slots
+        std::map<int64_t, int64_t> slots{{0, n_slots}};  // time free -> slots
         int64_t seen = 0, end = 0;
         for (int r = R; r >= 0; --r) {
             int64_t n = (seen + strips[r] + 3) / 4 - (seen + 3) / 4;
@@ -644,7 +645,7 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
     for (size_t k = 0; k < L.sizes.size(); k += 2)
         row_waves += (int64_t)feat_tiles_x(L.sizes[k] / PD_CELL) * (L.sizes[k + 1] / PD_CELL);
     R.feat_rows = !L.prune && row_waves <= FR_MAX_ROWS;
-    if (!R.feat_rows) R.strip_rows = tu.feat_rows ? tu.feat_rows : strip_rows(L);
+    if (!R.feat_rows) R.strip_rows = tu.feat_rows ? tu.feat_rows : strip_rows(L, features);
     const int rs_rows = resize_rows(L.n_rs);
     for (int f = 0; f < n_frames; ++f) {
         geoms[f].n_levels = L.level_count[f];
