@@ -6,146 +6,123 @@
 // recomputes such a window's features from the pixels of its pyramid level in
 // FP64 -- gradients (Algorithm 4; orientation and magnitude from a table of
 // every integer gradient, built in FP64 with the device's double atan2), trilinear
-// HOG votes (Algorithm 5) as per-cell direction partials, L2-Hys -- takes its
-// LBP counts (exact integers) from the feature planes, and scores every model
-// in FP64 with the FP32 weights.  A window whose FP64 score (max over models)
+// HOG votes (Algorithm 5) as per-cell direction partials, L2-Hys -- and its LBP
+// counts (exact integers), and scores every model in FP64 with the FP32 weights.  A window whose FP64 score (max over models)
 // exceeds the threshold is appended to the frame's candidate list.
 //
-// One workgroup per near window, in two passes over the window's cell rows
-// (rows 0..7, then 8..15), so that the FP64 partials of 9 cell rows at a time
-// fit in LDS beside the pixels and two workgroups share a CU:
-//  * pixels: the window's 130 x 66 pixels (with halo) in LDS;
-//  * votes: in a pass, the four lanes l, l + 16, l + 32, l + 48 of a wave own
-//    one of the pass's 64 cells, two pixel rows each; a lane sums its 16
-//    pixels' votes in registers (the linear orientation vote as a hat over
-//    the 9 bins, towards the 2 x 3 target cells its rows can reach), the four
-//    quarters meet through cross-lane exchanges in a fixed order and the
-//    cell's 81 direction partials are stored once (no read-modify-write in
-//    LDS), in a ring of 9 cell rows (row r at r % 9);
-//  * blocks: pass 1 builds block rows 0..6 (cell rows 0..7), pass 2 block rows
-//    7..14 (cell rows 7..15: row 7 is still in the ring); a lane per block
-//    sums the partials aimed at each slot (exactly Algorithm 5's votes),
-//    L2-Hys, and stores the block's 36 HOG values;
-//  * dot products: after each pass's blocks, all 256 lanes stride over its
-//    HOG values (and after pass 2 over the LBP counts, staged over the
-//    pixels) with coalesced FP32 weights (one model: 16 features in flight
-//    per lane; several: four consecutive features per lane and step, one
-//    16-byte weight load per model, 8 x 8 in flight), then a fixed-order
-//    reduction;
-//  * gathers: a thread issues all of its pixel (and LBP count) loads before
-//    it stores any of them in LDS, so each gather costs one memory latency;
-//    pixel rows and LBP runs are read as aligned 4-byte words where the
-//    window allows it.
+// A workgroup of two waves takes a near window, a lane one of its 128 cells and,
+// after the votes, the block whose top left cell that is:
+//  * pixels (130 x 66 with halo): gathered into LDS, every load of a thread in
+//    flight before its first store; as words at any alignment where the window
+//    allows it;
+//  * LBP: a lane codes its cell's pixels, four per word, and counts them in LDS
+//    (reading the counts from the feature planes, 944 runs of 8 bytes, each on a
+//    cache line of its own, took 15 to 50 thousand cycles);
+//  * votes: a row of 8 pixels is summed into 27 registers (3 target columns x 9
+//    bins, the linear orientation vote as a hat over the 9 bins), which then
+//    go to the two target rows with the row's weights; half a row's table
+//    entries are in flight during the other half's votes.  No sum crosses
+//    lanes;
+//  * blocks: a lane adds its right neighbour's partials (data-parallel moves)
+//    and those of the cell below (through LDS, first the votes upwards, then
+//    the cell's own), and normalises its block in registers;
+//  * dot products: all lanes stride over the features, four at a time, with
+//    coalesced weights (a lane's own block against its 36 weights, a cache line
+//    per lane and load, took 35000 cycles for 8 models), and a fixed-order
+//    reduction.
+//
+// What bounds it is the FP64 arithmetic of the votes (about 50 instructions per
+// pixel) and the two waves' latency; 38 KB of LDS and 256 registers leave room
+// for four windows per CU.  A workgroup of four waves with the partials of nine
+// cell rows in LDS (72 KB, two windows per CU; four lanes per cell, their sums
+// meeting in 162 cross-lane exchanges per half window; one wave building the
+// blocks) took 121 us for 1333 windows of one model and 94 for 663 of eight;
+// this takes 70 and 50 (330 windows of one model: 37 and 29).
+#include "lbp_codes.h"
 #include "pd_internal.h"
 
 namespace pd {
 namespace {
 
-typedef uint32_t __attribute__((aligned(1))) u32_any;
+__constant__ LbpTable kLbpRescore = make_lbp_table();
 
+typedef uint32_t __attribute__((aligned(1))) u32_any;
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr int RS_THREADS = PD_WIN_CELLS_Y * PD_WIN_CELLS_X;  // 128: a thread per cell
 constexpr int RS_PY = PD_WIN_H + 2;  // 130 pixel rows incl. halo
 constexpr int RS_PX = PD_WIN_W + 2;  // 66 pixel columns incl. halo
-constexpr int RS_CELLS = PD_WIN_CELLS_Y * PD_WIN_CELLS_X;  // 128
 
 // LDS pixel rows: byte RS_PX0 + c holds window column c - 1 (c = 0 .. 65),
-// so that a row's source bytes from an aligned word boundary land on aligned
-// LDS words
+// so that a row's source bytes from a word boundary of the window's columns
+// land on aligned LDS words, and a cell's 8 pixels are two of them
 constexpr int RS_PX0 = 3;
 constexpr int RS_ROW = 72;                 // 18 words per row
 constexpr int RS_ROW_WORDS = RS_ROW / 4;
 
-constexpr int RS_RING = 9;                                        // cell rows of partials in LDS
-constexpr int RS_BLK1 = (PD_WIN_CELLS_Y / 2 - 1) * PD_WIN_BLOCKS_X;  // pass 1: block rows 0..6 (49 blocks)
-constexpr int RS_BLK2 = PD_WIN_BLOCKS_Y * PD_WIN_BLOCKS_X - RS_BLK1;  // pass 2: block rows 7..14 (56)
-constexpr int RS_HOG1 = RS_BLK1 * PD_HOG_BLOCK;                    // HOG features of pass 1 (1764)
-
 struct RescoreShared {
     union {
-        uint8_t px[RS_PY][RS_ROW];   // the window's pixels (votes)
-        uint8_t lbp[PD_LBP_DIM];     // then its LBP counts, feature order (cell, bin)
-    } p;
-    double A[RS_RING * PD_WIN_CELLS_X][81];  // per cell: 3x3 target cells x 9 bins
-    double hog[RS_BLK2 * PD_HOG_BLOCK];      // one pass's normalised HOG values
-    double part[2][4][8];                    // per pass, wave, model
+        struct {
+            double below[18][RS_THREADS];  // a cell's votes for the blocks that begin in the row above
+            uint8_t px[RS_PY][RS_ROW];     // the window's pixels
+        };
+        double hog[PD_HOG_DIM];  // then its HOG values
+    };
+    uint32_t lbp[PD_LBP_DIM / 4];   // its LBP counts, bytes in feature order (cell, bin)
+    uint8_t bin[256];               // of a bit-reversed code
+    double part[RS_THREADS / 64][8];  // per wave and model
 };
 
-constexpr int RS_PX_PER_T = (RS_PY * RS_PX + 255) / 256;   // pixel bytes gathered per thread (border windows)
-constexpr int RS_PXW_PER_T = (RS_PY * RS_ROW_WORDS + 255) / 256;  // pixel words per thread (inner windows)
-constexpr int RS_LBP_RUNS = PD_LBP_BINS * PD_WIN_CELLS_Y;  // 8-byte runs: one plane row of the window
-constexpr int RS_RUNS_PER_T = (RS_LBP_RUNS + 255) / 256;
-
-// Per-model partial dot products of the window's features (LDS) with the
-// weights over features [k_begin, k_end) (the whole vector, or one feature
-// family), M = 1 or 8 models unrolled (models past n_models repeat the last
-// one; their sums are never read).  Thread t takes features k_begin + t +
-// 256 u; U features per step, so a thread's M * U weight loads are in flight
-// together.  Past k_end x is 0 and the weight index is clamped.
-template <int M>
-__device__ __forceinline__ void dot_models(RescoreShared& sm, const float* __restrict__ weights, int n_models,
-                                           int k_begin, int k_end, int hog_base, int pass, int t, int wave,
-                                           int lane) {
-    constexpr int U = M == 1 ? 16 : 3;
-    double part[M];
-#pragma unroll
-    for (int m = 0; m < M; ++m) part[m] = 0.0;
-    for (int k0 = k_begin + t; k0 < k_end; k0 += 256 * U) {
-        float w[U][M];
-        double x[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = k0 + 256 * u;
-            const int kc = min(k, k_end - 1);
-#pragma unroll
-            for (int m = 0; m < M; ++m) w[u][m] = weights[(size_t)min(m, n_models - 1) * PD_FEATURE_DIM + kc];
-            const double xv = kc < PD_HOG_DIM ? sm.hog[kc - hog_base] : (double)sm.p.lbp[kc - PD_HOG_DIM];
-            x[u] = k < k_end ? xv : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int m = 0; m < M; ++m) part[m] = fma(x[u], (double)w[u][m], part[m]);
-    }
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        double s = part[m];
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-        if (lane == 0) sm.part[pass][wave][m] = s;
-    }
+constexpr int RS_PX_PER_T = (RS_PY * RS_PX + RS_THREADS - 1) / RS_THREADS;   // pixel bytes per thread (border windows)
+constexpr int RS_PXW_PER_T = (RS_PY * RS_ROW_WORDS + RS_THREADS - 1) / RS_THREADS;  // pixel words per thread (inner)
+// Bilinear weight of pixel offset p in [0, 8) of a cell towards cell d in {-1, 0, 1}.
+__device__ __forceinline__ double spatial_w(int p, int d) {
+    const double w = 1.0 - fabs((double)p + 0.5 - (8.0 * d + 4.0)) / 8.0;
+    return w > 0.0 ? w : 0.0;
 }
 
-// The same with each thread taking four consecutive features per step
-// (groups g = g_begin + t + 256 u of 4: one 16-byte weight load per model;
-// 1764, 3780 and 11332 are multiples of 4, so a group is all HOG or all LBP
-// and lies in one pass).
-// Needs 16-byte aligned weights.
+// The value of the lane to the right (the cell to the right: rows of 8 cells lie
+// within a row of 16 lanes).
+__device__ __forceinline__ double right_lane(double v) {
+    const uint64_t u = __double_as_longlong(v);
+    constexpr int ROW_SHL1 = 0x101;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, ROW_SHL1, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), ROW_SHL1, 0xf, 0xf, true);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// Each model's dot product over the features [4 g_begin, 4 g_end), four at a time
+// (one 16-byte weight load per model; HOG and LBP begin at multiples of 4), U
+// groups per turn in flight together; M = 1 or 8 models unrolled (models past
+// n_models repeat the last one; their sums are never read).
 template <int M>
-__device__ __forceinline__ void dot_models4(RescoreShared& sm, const float4* __restrict__ w4, int n_models,
-                                            int g_begin, int g_end, int hog_base, int pass, int t, int wave,
-                                            int lane) {
-    constexpr int G = PD_FEATURE_DIM / 4;
-    constexpr int U = M == 1 ? 4 : 1;
+__device__ __forceinline__ void dot_models(RescoreShared& sm, const float* __restrict__ weights, int n_models,
+                                           int g_begin, int g_end, int t) {
+    static_assert(PD_HOG_DIM % 4 == 0 && PD_LBP_DIM % 4 == 0, "groups of one family");
+    constexpr int U = M == 1 ? 4 : 2;
     double part[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) part[m] = 0.0;
-    for (int g0 = g_begin + t; g0 < g_end; g0 += 256 * U) {
-        float4 w[U][M];
+#pragma unroll 1
+    for (int g0 = g_begin + t; g0 < g_end; g0 += RS_THREADS * U) {
+        f32x4_any w[U][M];
         double x[U][4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int g = g0 + 256 * u;
-            const int gc = min(g, g_end - 1);
+            const int g = min(g0 + RS_THREADS * u, g_end - 1);
 #pragma unroll
-            for (int m = 0; m < M; ++m) w[u][m] = w4[(size_t)min(m, n_models - 1) * G + gc];
-            const int k = 4 * gc;
-            if (k < PD_HOG_DIM) {
+            for (int m = 0; m < M; ++m)
+                w[u][m] = *reinterpret_cast<const f32x4_any*>(weights + (size_t)min(m, n_models - 1) * PD_FEATURE_DIM +
+                                                              4 * g);
+            if (g < PD_HOG_DIM / 4) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) x[u][j] = sm.hog[k - hog_base + j];
+                for (int j = 0; j < 4; ++j) x[u][j] = sm.hog[4 * g + j];
             } else {
-                const uint32_t b = *reinterpret_cast<const uint32_t*>(&sm.p.lbp[k - PD_HOG_DIM]);
+                const uint32_t b = sm.lbp[g - PD_HOG_DIM / 4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) x[u][j] = (double)((b >> (8 * j)) & 255u);
             }
-            if (g >= g_end) {
+            if (g0 + RS_THREADS * u >= g_end) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) x[u][j] = 0.0;
             }
@@ -153,41 +130,139 @@ __device__ __forceinline__ void dot_models4(RescoreShared& sm, const float4* __r
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int m = 0; m < M; ++m) {
-                part[m] = fma(x[u][0], (double)w[u][m].x, part[m]);
-                part[m] = fma(x[u][1], (double)w[u][m].y, part[m]);
-                part[m] = fma(x[u][2], (double)w[u][m].z, part[m]);
-                part[m] = fma(x[u][3], (double)w[u][m].w, part[m]);
-            }
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) part[m] = fma(x[u][j], (double)w[u][m][j], part[m]);
     }
 #pragma unroll
     for (int m = 0; m < M; ++m) {
         double s = part[m];
         for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-        if (lane == 0) sm.part[pass][wave][m] = s;
+        if ((t & 63) == 0) sm.part[t >> 6][m] = s;
     }
 }
 
-// Bilinear weight of pixel offset p in [0, 8) of a cell towards cell d in {-1, 0, 1}.
-__device__ __forceinline__ double spatial_w(int p, int d) {
-    const double w = 1.0 - fabs((double)p + 0.5 - (8.0 * d + 4.0)) / 8.0;
-    return w > 0.0 ? w : 0.0;
+// A row of a cell's neighbourhood: its 8 pixels and those shifted by one.
+struct LbpRow {
+    uint32_t own[2], left[2], right[2];
+    __device__ __forceinline__ void load(const uint8_t* p) {  // p: the first pixel, a word boundary
+        own[0] = *reinterpret_cast<const uint32_t*>(p);
+        own[1] = *reinterpret_cast<const uint32_t*>(p + 4);
+        left[0] = own[0] << 8 | p[-1];
+        left[1] = __builtin_amdgcn_alignbyte(own[1], own[0], 3);
+        right[0] = __builtin_amdgcn_alignbyte(own[1], own[0], 1);
+        right[1] = own[1] >> 8 | (uint32_t)p[8] << 24;
+    }
+};
+
+// Adds the codes of cell t to its counts (cells share words at their ends).
+__device__ __forceinline__ void count_lbp(RescoreShared& sm, int t) {
+    const int cy = t / PD_WIN_CELLS_X, cx = t % PD_WIN_CELLS_X;
+    const uint8_t* p = &sm.px[PD_CELL * cy][RS_PX0 + 1 + PD_CELL * cx];
+    LbpRow U, C, D, N;
+    U.load(p);
+    C.load(p + RS_ROW);
+    D.load(p + 2 * RS_ROW);
+#pragma unroll 2
+    for (int py = 0; py < PD_CELL; ++py) {
+        N.load(p + min(py + 3, PD_CELL + 1) * RS_ROW);
+#pragma unroll
+        for (int hw = 0; hw < 2; ++hw) {
+            // Algorithm 1's neighbours in its bit order
+            const uint32_t nb[8] = {U.left[hw],  U.own[hw], U.right[hw], C.right[hw],
+                                    D.right[hw], D.own[hw], D.left[hw],  C.left[hw]};
+            uint32_t r[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) r[k] = ge_bytes(nb[k], C.own[hw], C.own[hw] & 0x7f7f7f7fu);
+            const uint32_t code = lbp_codes4(r);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t e = PD_LBP_BINS * t + sm.bin[code >> (8 * u) & 255u];
+                atomicAdd(&sm.lbp[e >> 2], 1u << (8 * (e & 3u)));
+            }
+        }
+        U = C;
+        C = D;
+        D = N;
+    }
 }
 
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) rescore64_kernel(const LevelItem* __restrict__ items,
-                                                        const int32_t* __restrict__ first_item, int n_frames,
-                                                        const int32_t* __restrict__ near_count,
-                                                        const int4* __restrict__ near_key,
-                                                        const float* __restrict__ weights,
-                                                        const float* __restrict__ bias, int n_models, int features,
-                                                        double clip, double eps,
-                                                        const double* __restrict__ thresholds,
-                                                        int32_t* __restrict__ counters, float* __restrict__ cand_score,
-                                                        int4* __restrict__ cand_key, double* __restrict__ cand_s64,
-                                                        const double2* __restrict__ orient, bool vec_w) {
+// The votes of one cell (cy, cx), rows py0 .. py0 + 3 (a half): acc[0] towards
+// the cells of the row above (py0 = 0) or its own (4), acc[1] its own or the row
+// below; [dx + 1][bin].  Adds to acc.
+__device__ __forceinline__ void half_votes(const RescoreShared& sm, const double2* __restrict__ orient, int cy, int cx,
+                                           int py0, double (&acc)[2][3][PD_HOG_BINS]) {
+    // pixels px0 .. px0 + 3 of row py: their table entries
+    auto entries = [&](int py, int px0, double2 (&g)[4]) __attribute__((always_inline)) {
+        const uint8_t* const row = &sm.px[PD_CELL * cy + py + 1][RS_PX0 + 1 + PD_CELL * cx + px0];
+        const uint32_t up = *reinterpret_cast<const uint32_t*>(row - RS_ROW);
+        const uint32_t down = *reinterpret_cast<const uint32_t*>(row + RS_ROW);
+        const uint32_t own = *reinterpret_cast<const uint32_t*>(row);
+        const int left = row[-1], right = row[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int a = u > 0 ? (int)(own >> (8 * (u - 1)) & 255u) : left;
+            const int b = u < 3 ? (int)(own >> (8 * (u + 1)) & 255u) : right;
+            const int dx = a - b;  // Algorithm 4
+            const int dy = (int)(up >> (8 * u) & 255u) - (int)(down >> (8 * u) & 255u);
+            g[u] = orient[abs(dy) * ORIENT_W + (dy < 0 ? -dx : dx) + 255];
+        }
+    };
+    double R[3][PD_HOG_BINS];  // the row's sums
+    auto votes = [&](int px0, const double2 (&g)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double tb = g[u].x, mag = g[u].y;
+            const int q = px0 == 0 ? 0 : 1;  // target columns q - 1 and q (as dx)
+            const double m0 = mag * spatial_w(px0 + u, q - 1), m1 = mag * spatial_w(px0 + u, q);
+#pragma unroll
+            for (int k = 0; k < PD_HOG_BINS; ++k) {
+                // linear vote for the bin (wrap-around)
+                const double d = k == 0 ? fmin(fabs(tb), fabs(tb - 9.0))
+                                        : k == PD_HOG_BINS - 1 ? fmin(fabs(tb - 8.0), fabs(tb + 1.0))
+                                                               : fabs(tb - (double)k);
+                const double h = fmin(fmax(1.0 - d, 0.0), 1.0);  // one addition with its result clamped (d >= 0)
+                R[q][k] = fma(m0, h, R[q][k]);
+                R[q + 1][k] = fma(m1, h, R[q + 1][k]);
+            }
+        }
+    };
+    double2 g0[4], g1[4];
+    entries(py0, 0, g0);
+#pragma unroll 1
+    for (int py = py0; py < py0 + 4; ++py) {
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+#pragma unroll
+            for (int k = 0; k < PD_HOG_BINS; ++k) R[b][k] = 0.0;
+        entries(py, 4, g1);
+        votes(0, g0);
+        entries(min(py + 1, py0 + 3), 0, g0);
+        votes(4, g1);
+        const double w0 = spatial_w(py, (py0 >> 2) - 1), w1 = spatial_w(py, py0 >> 2);
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+#pragma unroll
+            for (int k = 0; k < PD_HOG_BINS; ++k) {
+                acc[0][b][k] = fma(w0, R[b][k], acc[0][b][k]);
+                acc[1][b][k] = fma(w1, R[b][k], acc[1][b][k]);
+            }
+    }
+}
+
+__global__ void __launch_bounds__(RS_THREADS) __attribute__((amdgpu_waves_per_eu(2))) rescore64_kernel(
+    const LevelItem* __restrict__ items, const int32_t* __restrict__ first_item, int n_frames,
+    const int32_t* __restrict__ near_count, const int4* __restrict__ near_key, const float* __restrict__ weights,
+    const float* __restrict__ bias, int n_models, int features, double clip, double eps,
+    const double* __restrict__ thresholds, int32_t* __restrict__ counters, float* __restrict__ cand_score,
+    int4* __restrict__ cand_key, double* __restrict__ cand_s64, const double2* __restrict__ orient) {
     __shared__ RescoreShared sm;
     const int t = threadIdx.x;
-    const int wave = t >> 6, lane = t & 63;
+    const bool use_hog = (features & PD_FEAT_HOG) != 0, use_lbp = (features & PD_FEAT_LBP) != 0;
+    const int cy = t / PD_WIN_CELLS_X, cx = t % PD_WIN_CELLS_X;
+    const int block = cy < PD_WIN_BLOCKS_Y && cx < PD_WIN_BLOCKS_X ? cy * PD_WIN_BLOCKS_X + cx : -1;
+    if (use_lbp)
+        for (int c = t; c < 256; c += RS_THREADS) sm.bin[c] = kLbpRescore.bin[__brev(c) >> 24];
     const int total = near_count[n_frames];  // dense list of every frame's near windows
     for (int q = blockIdx.x; q < total; q += gridDim.x) {
         const int4 key = near_key[q];
@@ -200,6 +275,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) r
         // registers across windows
         int tt = t;
         asm volatile("" : "+v"(tt));
+        if (use_lbp)
+            for (int e = tt; e < PD_LBP_DIM / 4; e += RS_THREADS) sm.lbp[e] = 0u;
         // pixels of the window + one halo pixel: every load of a thread in
         // flight together, then the LDS stores.  A window whose halo, and the
         // three pixels after it, lie inside the level reads words (at any
@@ -211,20 +288,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) r
             uint32_t v[RS_PXW_PER_T];
 #pragma unroll
             for (int k = 0; k < RS_PXW_PER_T; ++k) {
-                const int e = min(tt + 256 * k, RS_PY * RS_ROW_WORDS - 1);
+                const int e = min(tt + RS_THREADS * k, RS_PY * RS_ROW_WORDS - 1);
                 const int r = e / RS_ROW_WORDS, d = e - r * RS_ROW_WORDS;
                 v[k] = *reinterpret_cast<const u32_any*>(base + (size_t)r * it.pitch + 4 * d);
             }
 #pragma unroll
             for (int k = 0; k < RS_PXW_PER_T; ++k) {
-                const int e = tt + 256 * k;
-                if (e < RS_PY * RS_ROW_WORDS) reinterpret_cast<uint32_t*>(&sm.p.px[0][0])[e] = v[k];
+                const int e = tt + RS_THREADS * k;
+                if (e < RS_PY * RS_ROW_WORDS) reinterpret_cast<uint32_t*>(&sm.px[0][0])[e] = v[k];
             }
         } else {
             uint32_t v[RS_PX_PER_T];
 #pragma unroll
             for (int k = 0; k < RS_PX_PER_T; ++k) {
-                const int e = min(tt + 256 * k, RS_PY * RS_PX - 1);
+                const int e = min(tt + RS_THREADS * k, RS_PY * RS_PX - 1);
                 const int r = e / RS_PX, c = e - (e / RS_PX) * RS_PX;
                 const int y = min(max(PD_CELL * wi - 1 + r, 0), it.h - 1);
                 const int x = min(max(PD_CELL * wj - 1 + c, 0), it.w - 1);
@@ -232,187 +309,94 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) r
             }
 #pragma unroll
             for (int k = 0; k < RS_PX_PER_T; ++k) {
-                const int e = tt + 256 * k;
+                const int e = tt + RS_THREADS * k;
                 if (e < RS_PY * RS_PX) {
                     const int r = e / RS_PX, c = e - (e / RS_PX) * RS_PX;
-                    sm.p.px[r][RS_PX0 + c] = (uint8_t)v[k];
+                    sm.px[r][RS_PX0 + c] = (uint8_t)v[k];
                 }
             }
         }
         __syncthreads();
+        if (use_lbp) count_lbp(sm, t);
 
-        // LBP counts of the window's 16 x 8 cells: one run of 8 bytes per
-        // plane row, read as the aligned words that hold it (each holds a
-        // byte of the run, so none leaves the planes); issued here so that
-        // they arrive during the votes, stored over the pixels after them
-        uint32_t lw[RS_RUNS_PER_T][3];
-        uint32_t loff[RS_RUNS_PER_T];
-        {
-            const size_t plane = (size_t)it.hc * it.wc;
-#pragma unroll
-            for (int k = 0; k < RS_RUNS_PER_T; ++k) {
-                const int e = min(tt + 256 * k, RS_LBP_RUNS - 1);
-                const int bin = e / PD_WIN_CELLS_Y, a = e - bin * PD_WIN_CELLS_Y;
-                const uint8_t* p = it.lbp + bin * plane + (size_t)(wi + a) * it.wc + wj;
-                loff[k] = (uint32_t)(reinterpret_cast<uintptr_t>(p) & 3);
-                const uint32_t* q = reinterpret_cast<const uint32_t*>(p - loff[k]);
-                lw[k][0] = q[0];
-                lw[k][1] = q[1];
-                lw[k][2] = loff[k] ? q[2] : 0u;
-            }
-        }
-
-        // votes of cell rows 8 pass .. 8 pass + 7 into the ring of partials
-        auto votes = [&](int pass) __attribute__((always_inline)) {
-            const int quarter = lane >> 4;                    // pixel rows 2 quarter, 2 quarter + 1
-            const int half = quarter >> 1;                    // 0: rows 0..3, 1: rows 4..7
-            const int cell = wave * 16 + (lane & 15);         // of the pass's 64
-            const int cy = 8 * pass + cell / PD_WIN_CELLS_X, cx = cell - (cell / PD_WIN_CELLS_X) * PD_WIN_CELLS_X;
-            // acc[dy index][dx + 1][bin]; dy index 0/1 = dy -1/0 (top) or 0/+1 (bottom)
+        if (use_hog) {
+            // slot (r, c) of the block that begins at this cell: the four cells'
+            // partials aimed at it (exactly Algorithm 5's votes)
+            double v[PD_HOG_BLOCK];
+            // what the block's own row (this cell and the one to its right)
+            // gives its left (c = 0) and right (c = 1) column
+            auto pair = [](const double (&x)[3][PD_HOG_BINS], int c, int k) {
+                return x[1 + c][k] + right_lane(x[c][k]);
+            };
             double acc[2][3][PD_HOG_BINS];
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
+            auto clear = [&](int a) {
 #pragma unroll
                 for (int b = 0; b < 3; ++b)
 #pragma unroll
                     for (int k = 0; k < PD_HOG_BINS; ++k) acc[a][b][k] = 0.0;
-#pragma unroll 1
-            for (int pr = 0; pr < 2; ++pr) {
-                const int py = 2 * quarter + pr;
-                const double wy0 = spatial_w(py, half - 1), wy1 = spatial_w(py, half);
-                // the row's table entries, four in flight together
+            };
+            clear(0);
+            clear(1);
+            half_votes(sm, orient, cy, cx, 0, acc);
+            // acc[0]: votes upwards, for the blocks that begin in the row above
 #pragma unroll
-                for (int x4 = 0; x4 < PD_CELL; x4 += 4) {
-                    double2 g[4];
+            for (int c = 0; c < 2; ++c)
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int px = x4 + u;
-                        const int r = PD_CELL * cy + py + 1, c = PD_CELL * cx + px + 1;
-                        const int dx = (int)sm.p.px[r][RS_PX0 + c - 1] - (int)sm.p.px[r][RS_PX0 + c + 1];  // Algorithm 4
-                        const int dy = (int)sm.p.px[r - 1][RS_PX0 + c] - (int)sm.p.px[r + 1][RS_PX0 + c];
-                        const int s = dy < 0 ? -1 : 1;
-                        g[u] = orient[(s * dy) * ORIENT_W + s * dx + 255];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int px = x4 + u;
-                        const double tb = g[u].x, mag = g[u].y;
-                        double h[PD_HOG_BINS];                         // linear vote per bin (wrap-around)
-                        h[0] = fmax(0.0, 1.0 - fmin(fabs(tb), fabs(tb - 9.0)));
-#pragma unroll
-                        for (int k = 1; k < PD_HOG_BINS - 1; ++k) h[k] = fmax(0.0, 1.0 - fabs(tb - (double)k));
-                        h[8] = fmax(0.0, 1.0 - fmin(fabs(tb - 8.0), fabs(tb + 1.0)));
-                        const int q0 = px < 4 ? 0 : 1;                 // target columns q0 - 1 and q0 (as dx)
-                        const double wx0 = spatial_w(px, q0 - 1), wx1 = spatial_w(px, q0);
-                        const double m0 = mag * wy0, m1 = mag * wy1;
-#pragma unroll
-                        for (int k = 0; k < PD_HOG_BINS; ++k) {
-                            acc[0][q0][k] = fma(m0 * wx0, h[k], acc[0][q0][k]);
-                            acc[0][q0 + 1][k] = fma(m0 * wx1, h[k], acc[0][q0 + 1][k]);
-                            acc[1][q0][k] = fma(m1 * wx0, h[k], acc[1][q0][k]);
-                            acc[1][q0 + 1][k] = fma(m1 * wx1, h[k], acc[1][q0 + 1][k]);
-                        }
-                    }
-                }
-            }
-            // the quarters meet: dy = -1 = top quarters' acc[0], dy = 0 = top
-            // quarters' acc[1] + bottom quarters' acc[0], dy = +1 = bottom
-            // quarters' acc[1]; quarter 0 stores dy = -1, quarter 1 dy = 0,
-            // quarter 2 dy = +1
-            double* A = sm.A[(cy % RS_RING) * PD_WIN_CELLS_X + cx];
+                for (int k = 0; k < PD_HOG_BINS; ++k) sm.below[c * PD_HOG_BINS + k][t] = pair(acc[0], c, k);
 #pragma unroll
             for (int b = 0; b < 3; ++b)
 #pragma unroll
-                for (int k = 0; k < PD_HOG_BINS; ++k) {
-                    const double p0 = acc[0][b][k] + __shfl_xor(acc[0][b][k], 16, 64);  // quarter pair sums
-                    const double p1 = acc[1][b][k] + __shfl_xor(acc[1][b][k], 16, 64);
-                    const double other0 = __shfl_xor(p0, 32, 64);                     // the other half's
-                    if (quarter == 0) A[(0 * 3 + b) * PD_HOG_BINS + k] = p0;          // dy = -1
-                    if (quarter == 1) A[(1 * 3 + b) * PD_HOG_BINS + k] = p1 + other0; // dy = 0
-                    if (quarter == 2) A[(2 * 3 + b) * PD_HOG_BINS + k] = p1;          // dy = +1
-                }
-        };
-        // blocks of block rows by0 .. (lane t < n): slot (r, c) of block (by,
-        // bx) sums the partials its 4 cells aim at it; L2-Hys; stored at
-        // sm.hog[t * 36 ..]
-        auto blocks = [&](int by0, int n) __attribute__((always_inline)) {
-            if (t >= n) return;
-            const int by = by0 + t / PD_WIN_BLOCKS_X, bx = t - (t / PD_WIN_BLOCKS_X) * PD_WIN_BLOCKS_X;
-            double v[PD_HOG_BLOCK];
-            for (int r = 0; r < 2; ++r)
-                for (int c = 0; c < 2; ++c)
-                    for (int k = 0; k < PD_HOG_BINS; ++k) {
-                        double s = 0.0;
-                        for (int sy = 0; sy < 2; ++sy)
-                            for (int sx = 0; sx < 2; ++sx)
-                                s += sm.A[((by + sy) % RS_RING) * PD_WIN_CELLS_X + (bx + sx)]
-                                         [((r - sy + 1) * 3 + (c - sx + 1)) * PD_HOG_BINS + k];
-                        v[(r * 2 + c) * PD_HOG_BINS + k] = s;
-                    }
+                for (int k = 0; k < PD_HOG_BINS; ++k) acc[0][b][k] = acc[1][b][k];
+            clear(1);
+            half_votes(sm, orient, cy, cx, 4, acc);
+            // acc[0]: votes for the cell's own row, acc[1]: downwards
+            const int under = min(t + PD_WIN_CELLS_X, RS_THREADS - 1);
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int k = 0; k < PD_HOG_BINS; ++k)
+                    v[c * PD_HOG_BINS + k] = pair(acc[0], c, k) + sm.below[c * PD_HOG_BINS + k][under];
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int k = 0; k < PD_HOG_BINS; ++k) sm.below[c * PD_HOG_BINS + k][t] = pair(acc[0], c, k);
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int k = 0; k < PD_HOG_BINS; ++k)
+                    v[(2 + c) * PD_HOG_BINS + k] = pair(acc[1], c, k) + sm.below[c * PD_HOG_BINS + k][under];
             double ss = 0.0;
+#pragma unroll
             for (int k = 0; k < PD_HOG_BLOCK; ++k) ss += v[k] * v[k];
             double inv = 1.0 / sqrt(ss + eps * eps);
             double ss2 = 0.0;
+#pragma unroll
             for (int k = 0; k < PD_HOG_BLOCK; ++k) {
                 v[k] = fmin(v[k] * inv, clip);
                 ss2 += v[k] * v[k];
             }
             inv = 1.0 / sqrt(ss2 + eps * eps);
-            for (int k = 0; k < PD_HOG_BLOCK; ++k) sm.hog[t * PD_HOG_BLOCK + k] = v[k] * inv;
-        };
-        // dot products over features [k_begin, k_end) (whole features of this
-        // pass, or of the one family of an HOG-only / LBP-only detector), all
-        // lanes, coalesced weights from the L2, a fixed-order reduction
-        auto dot = [&](int k_begin, int k_end, int hog_base, int pass) __attribute__((always_inline)) {
-            if (vec_w && n_models > 1) {
-                dot_models4<8>(sm, reinterpret_cast<const float4*>(weights), n_models, k_begin / 4, k_end / 4,
-                               hog_base, pass, t, wave, lane);
-            } else if (n_models == 1) {
-                dot_models<1>(sm, weights, 1, k_begin, k_end, hog_base, pass, t, wave, lane);
-            } else {
-                dot_models<8>(sm, weights, n_models, k_begin, k_end, hog_base, pass, t, wave, lane);
-            }
-        };
-        const bool use_hog = (features & PD_FEAT_HOG) != 0, use_lbp = (features & PD_FEAT_LBP) != 0;
-
-        // pass 1: cell rows 0..7, block rows 0..6
-        votes(0);
-        __syncthreads();
-        blocks(0, RS_BLK1);
-        __syncthreads();
-        dot(0, use_hog ? RS_HOG1 : 0, 0, 0);
-        // pass 2: cell rows 8..15 (over rows 0..6 of the ring, after the
-        // barrier above), block rows 7..14
-        votes(1);
-        __syncthreads();  // the pass's partials are stored, the pixels and the pass-1 HOG values read
-        blocks(PD_WIN_CELLS_Y / 2 - 1, RS_BLK2);
-        {
 #pragma unroll
-            for (int k = 0; k < RS_RUNS_PER_T; ++k) {
-                const int e = tt + 256 * k;
-                if (e < RS_LBP_RUNS) {
-                    const int bin = e / PD_WIN_CELLS_Y, a = e - bin * PD_WIN_CELLS_Y;
-                    const uint32_t lo = __builtin_amdgcn_alignbyte(lw[k][1], lw[k][0], loff[k]);
-                    const uint32_t hi = __builtin_amdgcn_alignbyte(lw[k][2], lw[k][1], loff[k]);
-                    uint8_t* dst = &sm.p.lbp[(a * PD_WIN_CELLS_X) * PD_LBP_BINS + bin];
+            for (int k = 0; k < PD_HOG_BLOCK; ++k) v[k] *= inv;
+            __syncthreads();  // the votes (and pixels) are read
+            if (block >= 0) {
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        dst[b * PD_LBP_BINS] = (uint8_t)(lo >> (8 * b));
-                        dst[(b + 4) * PD_LBP_BINS] = (uint8_t)(hi >> (8 * b));
-                    }
-                }
+                for (int k = 0; k < PD_HOG_BLOCK; ++k) sm.hog[block * PD_HOG_BLOCK + k] = v[k];
             }
         }
         __syncthreads();
-        dot(use_hog ? RS_HOG1 : PD_HOG_DIM, use_lbp ? PD_FEATURE_DIM : PD_HOG_DIM, RS_HOG1, 1);
+        const int g_begin = use_hog ? 0 : PD_HOG_DIM / 4, g_end = use_lbp ? PD_FEATURE_DIM / 4 : PD_HOG_DIM / 4;
+        if (n_models == 1) dot_models<1>(sm, weights, 1, g_begin, g_end, t);
+        else dot_models<8>(sm, weights, n_models, g_begin, g_end, t);
         __syncthreads();
         if (t == 0) {
             double best = 0.0;
             int bm = 0;
             for (int m = 0; m < n_models; ++m) {
-                const double s1 = (sm.part[0][0][m] + sm.part[0][1][m]) + (sm.part[0][2][m] + sm.part[0][3][m]);
-                const double s2 = (sm.part[1][0][m] + sm.part[1][1][m]) + (sm.part[1][2][m] + sm.part[1][3][m]);
-                const double s = (s1 + s2) + (double)bias[m];
+                const double s = (sm.part[0][m] + sm.part[1][m]) + (double)bias[m];
                 if (m == 0 || s > best) {
                     best = s;
                     bm = m;
@@ -440,12 +424,12 @@ hipError_t launch_rescore64(const LevelItem* items, const int32_t* frame_first_i
                             int32_t* counters, float* cand_score, int4* cand_key, double* cand_s64,
                             const double2* orient, hipStream_t s) {
     if (n_frames <= 0) return hipSuccess;
-    // persistent workgroups (two per CU fit the LDS) over the dense near
-    // list, whose length is read on the device
+    // persistent workgroups (four per CU) over the dense near list, whose length
+    // is read on the device
     const int grid = 1024;
-    rescore64_kernel<<<grid, 256, 0, s>>>(items, frame_first_item, n_frames, near_count, near_key, weights, bias,
+    rescore64_kernel<<<grid, RS_THREADS, 0, s>>>(items, frame_first_item, n_frames, near_count, near_key, weights, bias,
                                          n_models, features, (double)clip, (double)eps, thresholds, counters,
-                                         cand_score, cand_key, cand_s64, orient, ((uintptr_t)weights & 15) == 0);
+                                         cand_score, cand_key, cand_s64, orient);
     return hipGetLastError();
 }
 
