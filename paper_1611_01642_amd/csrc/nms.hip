@@ -4,7 +4,7 @@
 // compact: four windows per thread, their loads in flight together; a
 //   window's score is the max over the models (lowest model index on ties);
 //   windows with score > threshold are appended to their frame's candidate
-//   list with an atomic counter.  A frame's list has room for every one of
+//   list, a workgroup's together, with an atomic counter.  A frame's list has room for every one of
 //   its windows, so none is dropped.
 // select (in the NMS kernel): for a frame with more than PD_MAX_CANDIDATES candidates, the
 //   PD_MAX_CANDIDATES highest-scoring ones (score descending, then level, i,
@@ -40,7 +40,7 @@ __global__ void __launch_bounds__(CP_THREADS) compact_kernel(const LevelItem* __
     const LevelItem& it = items[tl.item];
     const int n = it.nx * it.ny;
     const int q0 = tl.tx * CP_N + threadIdx.x;
-    if (q0 >= n) return;
+    __shared__ int sums[2][CP_THREADS / 64], bases[2];
     // windows q0 + k * CP_THREADS: every load is issued before the first
     // decision (windows past the level read its last one and are skipped)
     int qk[CP_PER];
@@ -69,21 +69,58 @@ __global__ void __launch_bounds__(CP_THREADS) compact_kernel(const LevelItem* __
         }
     }
     const double thr = thresholds[it.frame];
+    // near: too close to call in this precision, rescored in FP64.  A workgroup's
+    // windows are of one frame, so it adds to each counter once: additions to the
+    // same word follow one another (1.2 million windows, 1% of them listed: one
+    // per window 37 us, per wave 27, per workgroup 15)
+    uint64_t near[CP_PER], over[CP_PER];
+    int n_near = 0, n_over = 0;
 #pragma unroll
     for (int k = 0; k < CP_PER; ++k) {
-        const int q = q0 + k * CP_THREADS;
-        if (q >= n || !keep[k]) continue;
-        const int i = q / it.nx;
-        if (margin > 0.0f && fabs((double)best[k] - thr) < (double)margin) {
-            // too close to call in this precision: rescored in FP64.  near_count
-            // holds one counter per frame and, after them, the length of the
-            // dense list of all frames' near windows (room for every window of
-            // the batch: the bound is never reached)
-            atomicAdd(&near_count[it.frame], 1);
-            const int g = atomicAdd(&near_count[n_frames], 1);
+        const bool in = q0 + k * CP_THREADS < n && keep[k];
+        const bool close = margin > 0.0f && fabs((double)best[k] - thr) < (double)margin;
+        near[k] = __ballot(in && close);
+        over[k] = __ballot(in && !close && (double)best[k] > thr);
+        n_near += __popcll(near[k]);
+        n_over += __popcll(over[k]);
+    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (lane == 0) {
+        sums[0][wave] = n_near;
+        sums[1][wave] = n_over;
+    }
+    __syncthreads();
+    int at_near = 0, at_over = 0, all_near = 0, all_over = 0;
+#pragma unroll
+    for (int v = 0; v < CP_THREADS / 64; ++v) {
+        at_near += v < wave ? sums[0][v] : 0;
+        at_over += v < wave ? sums[1][v] : 0;
+        all_near += sums[0][v];
+        all_over += sums[1][v];
+    }
+    if (all_near + all_over == 0) return;  // the whole workgroup
+    if (threadIdx.x == 0) {
+        // near_count holds one counter per frame and, after them, the length of
+        // the dense list of all frames' near windows
+        if (all_near) {
+            bases[0] = atomicAdd(&near_count[n_frames], all_near);
+            atomicAdd(&near_count[it.frame], all_near);
+        }
+        if (all_over) bases[1] = atomicAdd(&counters[it.frame], all_over);
+    }
+    __syncthreads();
+    at_near += bases[0];
+    at_over += bases[1];
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int k = 0; k < CP_PER; ++k) {
+        const int q = q0 + k * CP_THREADS, i = q / it.nx;
+        if ((near[k] >> lane) & 1ull) {
+            // (room for every window of the batch: the bound is never reached)
+            const int g = at_near + __popcll(near[k] & below);
             if (g < near_cap) near_key[g] = make_int4(it.frame * PD_MAX_LEVELS + it.level, i, q - i * it.nx, bm[k]);
-        } else if ((double)best[k] > thr) {
-            const int pos = atomicAdd(&counters[it.frame], 1);
+        } else if ((over[k] >> lane) & 1ull) {
+            const int pos = at_over + __popcll(over[k] & below);
             if (pos < it.cand_cap) {  // always: a window is appended once at most
                 const size_t o = (size_t)it.cand_off + pos;
                 cand_score[o] = best[k];
@@ -91,6 +128,8 @@ __global__ void __launch_bounds__(CP_THREADS) compact_kernel(const LevelItem* __
                 if (cand_s64) cand_s64[o] = __longlong_as_double(0x7ff8000000000000LL);
             }
         }
+        at_near += __popcll(near[k]);
+        at_over += __popcll(over[k]);
     }
 }
 
