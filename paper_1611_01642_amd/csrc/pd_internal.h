@@ -198,7 +198,8 @@ __host__ __device__ inline int resize_tiles_y(int h) { return ceil_div(h, RS_TY)
 // are four per CU).  us at 16 / 32 / 64 rows: one 1242x375 frame (700 tiles)
 // 7.8 / 9.2 / 13.0, 4 frames 13.7 / 13.0 / 14.9, 16 (11200 tiles) 30.9 / 29.9 /
 // 29.4, 64 frames 112.5 / 101.6 / 96.2, 256 421 / 376 / 362 (128 rows: 368),
-// all before the next row's loads had registers of their own (64: 354).
+// all with unaligned loads and before the next row's loads had registers of
+// their own (64 rows now: 311).
 inline int resize_rows(int64_t tiles) { return tiles <= 1024 ? RS_TY : tiles <= 8192 ? 2 * RS_TY : 4 * RS_TY; }
 __host__ __device__ inline int feat_tiles_x(int wc) { return wc <= 1 ? 1 : ceil_div(wc - 1, FT_BX); }
 // Strips that also emit the pruner cell map own 62 columns: every owned cell

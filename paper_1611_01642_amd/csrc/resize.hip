@@ -7,18 +7,20 @@
 // down the rows.  The horizontal pass of a source row, (256 - fx) p0 + fx p1 per
 // column, is one dot product of the bytes (p0, p0, p1) with (255 - fx, 1, fx),
 // picked by one byte permutation out of 8 source bytes that the lane loads
-// itself, + 128 (one load for all four columns up to a scale of 2, one for two columns
-// up to 6, else one each; any alignment, always inside the row).  An output row
-// is then (256 - fy) top + fy bot, the two 128 giving the rounding's 2^15 (the
-// sum is below 2^25); the lower row's horizontal pass serves the next output row where that starts on it (9 of 10
+// itself, + 128 (one load for all four columns up to a scale of 2, one for two
+// columns up to 6, else one each: the three words that hold the 8 bytes, shifted;
+// words past the row read as 0).  An output row is then (256 - fy) top + fy bot,
+// the two 128 giving the rounding's 2^15 (the sum is below 2^25); the lower row's
+// horizontal pass serves the next output row where that starts on it (9 of 10
 // rows at a scale of 1.1, half of them at 1.5), and the next output row's loads
 // are in flight during the current one's arithmetic.
 //
 // No LDS and no barrier.  Staging the tile's source rectangle in LDS took 389
 // us for 256 frames of 1242x375 and 569 us for 64 of 1920x1080 (149 of the 389
-// for a tile's set-up and barriers); this takes 354 and 444.  What bounds it now
-// is the loads: 277 us with every row read from L1, 275 without stores, 251
-// without both, and no change from 4 of 37 vector instructions fewer.
+// for a tile's set-up and barriers); loading the 8 bytes at any alignment 354 and
+// 444 (an unaligned load takes a third more of the vector memory unit's time
+// than the same load from a word boundary); this takes 311 and 400, bound by
+// that unit and the loads' latency.
 #include "pd_internal.h"
 
 namespace pd {
@@ -39,7 +41,7 @@ __device__ __forceinline__ uint32_t q8_coord(int x, int n0, int nk) {
     return (uint32_t)q + (r >= k ? 1u : 0u) - (r < 0.0 ? 1u : 0u);
 }
 
-typedef uint64_t __attribute__((aligned(1))) u64_any;
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 
 // The walk: columns x0 .. x0 + 3 of the lane, rows y0 .. y1 - 1 (at most 64),
 // NL loads per source row.
@@ -58,33 +60,40 @@ __device__ __forceinline__ void resize_walk(gptr<const uint8_t> __restrict__ src
     for (int q = 0; q < 4; ++q) {
         const uint32_t c = q8_coord(min(x0 + q, w - 1), sw, w);
         const int xa = (int)(c >> 8);
-        if (q % CPL == 0) start[q / CPL] = (uint32_t)min(xa, sw - 8);
+        if (q % CPL == 0) start[q / CPL] = (uint32_t)xa;
         const uint32_t f = xa + 1 < sw ? c & 255u : 0u, o = (uint32_t)xa - start[q / CPL];
         wt[q] = (255u - f) | 1u << 8 | f << 16;
-        sel[q] = o | o << 8 | min(o + 1u, 7u) << 16 | 0x0c000000u;
+        sel[q] = o | o << 8 | (o + 1u) << 16 | 0x0c000000u;
         if (x0 + q < w) keep |= 255u << (8 * q);
     }
     // row coordinates, lane r: row y0 + r
     const uint32_t rows = q8_coord(min(y0 + lane, h - 1), sh, h);
     struct Raw {
-        uint64_t v[NL];
+        u32x3 v[NL];
+        uint32_t mis;  // the row's bytes past a word boundary
     };
     auto fetch = [&](int y, Raw& o) __attribute__((always_inline)) {
-        const auto row = src + (size_t)y * spitch;
+        const auto row = reinterpret_cast<uintptr_t>(src + (size_t)y * spitch);
+        o.mis = (uint32_t)row & 3u;
+        const auto rsrc = planes_rsrc(reinterpret_cast<const void*>(row - o.mis), (o.mis + (uint32_t)sw + 3u) & ~3u);
 #pragma unroll
         for (int k = 0; k < NL; ++k) {
-            uint32_t off = start[k];
-            asm volatile("" : "+v"(off));  // scalar base + 32-bit offset, widened by the load itself
-            o.v[k] = *reinterpret_cast<gptr<const u64_any>>(row + off);
+            const uint32_t off = (start[k] + o.mis) & ~3u;
+            o.v[k] = __builtin_amdgcn_raw_buffer_load_b96(rsrc, off, 0, 0);
+            asm volatile("" ::"v"(off));  // a register of its own (in the load's, it would wait for the last one)
         }
     };
     auto horizontal = [&](const Raw& r, uint32_t (&o)[4]) __attribute__((always_inline)) {
+        uint32_t lo[NL], hi[NL];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint64_t v = r.v[q / CPL];
-            o[q] = __builtin_amdgcn_udot4(__builtin_amdgcn_perm((uint32_t)(v >> 32), (uint32_t)v, sel[q]), wt[q],
-                                          128u, false);
+        for (int k = 0; k < NL; ++k) {
+            const uint32_t mis = (start[k] + r.mis) & 3u;
+            lo[k] = __builtin_amdgcn_alignbyte(r.v[k].y, r.v[k].x, mis);
+            hi[k] = __builtin_amdgcn_alignbyte(r.v[k].z, r.v[k].y, mis);
         }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            o[q] = __builtin_amdgcn_udot4(__builtin_amdgcn_perm(hi[q / CPL], lo[q / CPL], sel[q]), wt[q], 128u, false);
     };
     // uniform: source row and weight of output row r; the lower source row
     auto coord = [&](int r) { return (uint32_t)__builtin_amdgcn_readlane(rows, r); };
@@ -143,30 +152,9 @@ __device__ __forceinline__ void resize_tile(gptr<const uint8_t> __restrict__ src
     const int per = (rows + 3) >> 2;
     const int y0 = y_base + wave * per, y1 = min(min(y0 + per, y_base + rows), h);
     if (y0 >= y1) return;
-    if (sw >= 8 && sw <= 2 * w) {
-        resize_walk<1>(src, sw, sh, spitch, dst, w, h, pitch, x0, y0, y1);
-    } else if (sw >= 8 && sw <= 6 * w) {
-        resize_walk<2>(src, sw, sh, spitch, dst, w, h, pitch, x0, y0, y1);
-    } else if (sw >= 8) {
-        resize_walk<4>(src, sw, sh, spitch, dst, w, h, pitch, x0, y0, y1);
-    } else if (x0 < w) {
-        // images narrower than a load: (256-fx)(256-fy) p00 + fx (256-fy) p01 +
-        // (256-fx) fy p10 + fx fy p11, + 2^15, >> 16, grouped by row
-        for (int y = y0; y < y1; ++y) {
-            const uint32_t sy = q8_coord(y, sh, h);
-            const int ya = (int)(sy >> 8), yb = min(ya + 1, sh - 1), fy = (int)(sy & 255);
-            const auto ra = src + (size_t)ya * spitch, rb = src + (size_t)yb * spitch;
-            uint32_t packed = 0u;
-            for (int q = 0; q < 4 && x0 + q < w; ++q) {
-                const uint32_t sx = q8_coord(x0 + q, sw, w);
-                const int xa = (int)(sx >> 8), xb = min(xa + 1, sw - 1), fx = (int)(sx & 255);
-                const int top = (256 - fx) * (int)ra[xa] + fx * (int)ra[xb];
-                const int bot = (256 - fx) * (int)rb[xa] + fx * (int)rb[xb];
-                packed |= (uint32_t)(((256 - fy) * top + fy * bot + (1 << 15)) >> 16) << (8 * q);
-            }
-            *reinterpret_cast<gptr<uint32_t>>(dst + (size_t)y * pitch + x0) = packed;
-        }
-    }
+    if (sw <= 2 * w) resize_walk<1>(src, sw, sh, spitch, dst, w, h, pitch, x0, y0, y1);
+    else if (sw <= 6 * w) resize_walk<2>(src, sw, sh, spitch, dst, w, h, pitch, x0, y0, y1);
+    else resize_walk<4>(src, sw, sh, spitch, dst, w, h, pitch, x0, y0, y1);
 }
 
 struct ResizeArgs {
