@@ -127,7 +127,6 @@ template <int FEAT, bool CM>
 struct Lane {
     static constexpr bool DO_HOG = (FEAT & PD_FEAT_HOG) != 0;
     static constexpr bool DO_LBP = (FEAT & PD_FEAT_LBP) != 0;
-    static_assert(!CM || (DO_HOG && DO_LBP), "the cell map needs HOG and LBP");
     gptr<const uint8_t> img;
     int w, h, pitch;
     gptr<float> hog;
@@ -582,11 +581,11 @@ __host__ __device__ constexpr int row_chunk(int R) {
     return CM ? R - 2 : (FEAT & PD_FEAT_HOG) ? R - 1 : R;
 }
 
-template <int FEAT, bool CM, int RW>
+template <int FEAT, int PART, bool CM, int RW>
 __device__ __forceinline__ void features_rows(const LevelItem& it, int cy0, int tx, int width, float clip, float eps,
                                               FeatShared<FEAT, RW>& sm) {
-    constexpr bool DO_HOG = (FEAT & PD_FEAT_HOG) != 0, DO_LBP = (FEAT & PD_FEAT_LBP) != 0;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr bool DO_HOG = (PART & PD_FEAT_HOG) != 0, DO_LBP = (PART & PD_FEAT_LBP) != 0;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % RW;
     const int w = it.w, h = it.h, hc = it.hc, wc = it.wc, hb = hc - 1, wb = wc - 1;
     const int G = CM ? 1 : 64 / width, R = RW * G;
     const int li = CM ? lane : lane & (width - 1), g = CM ? 0 : lane / width;
@@ -599,8 +598,8 @@ __device__ __forceinline__ void features_rows(const LevelItem& it, int cy0, int 
     const bool blk_col = CM ? (own && cx < wb) : (li < width - 1 && cx < wb);
     const bool in = cy >= 0 && cy < hc;
     // the rows whose LBP counts (and cell map) this workgroup stores
-    const bool own_row = in && (CM ? rr >= 1 && rr < R - 1 : !DO_HOG || rr < R - 1 || cy == hc - 1);
-    const Lane<FEAT, CM> L{gmem(it.pyr), w, h, it.pitch, gmem(it.hog), gmem(it.hog16), gmem(it.lbp), gmem(it.cmap),
+    const bool own_row = in && (CM ? rr >= 1 && rr < R - 1 : !(FEAT & PD_FEAT_HOG) || rr < R - 1 || cy == hc - 1);
+    const Lane<PART, CM> L{gmem(it.pyr), w, h, it.pitch, gmem(it.hog), gmem(it.hog16), gmem(it.lbp), gmem(it.cmap),
                            gmem(it.cmap16), clip, eps, hc, wc, hb, wb, cx, x0, own, sm.lut,
                            &sm.cnt[wave][lane * LBP_WORDS], &sm.vote[wave][0][lane]};
     float T[3][PD_HOG_BINS], D9[3][PD_HOG_BINS], O[3][PD_HOG_BINS];  // votes towards cell rows cy - 1, cy + 1 and cy
@@ -638,7 +637,10 @@ __device__ __forceinline__ void features_rows(const LevelItem& it, int cy0, int 
         }
         if (DO_LBP && own_row && lbp_col) L.store_lbp(cy);
     }
-    if (!DO_HOG) return;
+    if (!DO_HOG) {
+        if (FEAT & PD_FEAT_HOG) __syncthreads();  // the one below
+        return;
+    }
     if (CM && !in) {  // rows outside the level vote for nothing
 #pragma unroll
         for (int a = 0; a < 3; ++a)
@@ -726,9 +728,25 @@ __device__ inline void init_lut(uint32_t (&lut)[256]) {
     __syncthreads();
 }
 
+// With both families, waves RW .. 2 RW - 1 take the LBP of the rows whose HOG
+// waves 0 .. RW - 1 take.
+template <int FEAT, int RW>
+constexpr int ROW_THREADS = 64 * RW * (FEAT == (PD_FEAT_HOG | PD_FEAT_LBP) ? 2 : 1);
+
+template <int FEAT, bool CM, int RW>
+__device__ __forceinline__ void features_rows_wave(const LevelItem& it, int cy0, int tx, int width, float clip,
+                                                   float eps, FeatShared<FEAT, RW>& sm) {
+    if constexpr (FEAT != (PD_FEAT_HOG | PD_FEAT_LBP))
+        features_rows<FEAT, FEAT, CM, RW>(it, cy0, tx, width, clip, eps, sm);
+    else if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < RW)
+        features_rows<FEAT, PD_FEAT_HOG, CM, RW>(it, cy0, tx, width, clip, eps, sm);
+    else
+        features_rows<FEAT, PD_FEAT_LBP, CM, RW>(it, cy0, tx, width, clip, eps, sm);
+}
+
 // One image: block x = strip, block y = chunk of rows.
 template <int FEAT, bool CM, int RW>
-__global__ void __launch_bounds__(RW * 64) features_rows_single_kernel(LevelItem it, float clip, float eps) {
+__global__ void __launch_bounds__((ROW_THREADS<FEAT, RW>)) features_rows_single_kernel(LevelItem it, float clip, float eps) {
     __shared__ FeatShared<FEAT, RW> sm;
     int width = 64;
     if (!CM) {
@@ -737,14 +755,14 @@ __global__ void __launch_bounds__(RW * 64) features_rows_single_kernel(LevelItem
     }
     const int cy0 = blockIdx.y * row_chunk<FEAT, CM>(RW * (64 / width));
     if (cy0 > 0 && cy0 >= ((FEAT & PD_FEAT_HOG) && !CM ? it.hc - 1 : it.hc)) return;
-    init_lut<RW * 64>(sm.lut);
-    features_rows<FEAT, CM, RW>(it, cy0, blockIdx.x, width, clip, eps, sm);
+    init_lut<ROW_THREADS<FEAT, RW>>(sm.lut);
+    features_rows_wave<FEAT, CM, RW>(it, cy0, blockIdx.x, width, clip, eps, sm);
 }
 
 // Table entry: item, ty = the first cell row, tx = strip, pad = lane-group
 // width; block y takes one of its FR_SPAN chunks of rows.
 template <int FEAT, int RW>
-__global__ void __launch_bounds__(RW * 64) features_rows_table_kernel(const LevelItem* __restrict__ items,
+__global__ void __launch_bounds__((ROW_THREADS<FEAT, RW>)) features_rows_table_kernel(const LevelItem* __restrict__ items,
                                                                       const Tile* __restrict__ tiles, float clip,
                                                                       float eps) {
     __shared__ FeatShared<FEAT, RW> sm;
@@ -752,8 +770,8 @@ __global__ void __launch_bounds__(RW * 64) features_rows_table_kernel(const Leve
     const LevelItem& it = items[tl.item];
     const int cy0 = tl.ty + blockIdx.y * row_chunk<FEAT, false>(RW * (64 / tl.pad));
     if (cy0 > 0 && cy0 >= ((FEAT & PD_FEAT_HOG) ? it.hc - 1 : it.hc)) return;
-    init_lut<RW * 64>(sm.lut);
-    features_rows<FEAT, false, RW>(it, cy0, tl.tx, tl.pad, clip, eps, sm);
+    init_lut<ROW_THREADS<FEAT, RW>>(sm.lut);
+    features_rows_wave<FEAT, false, RW>(it, cy0, tl.tx, tl.pad, clip, eps, sm);
 }
 
 __global__ void __launch_bounds__(FT_WAVES * 64) cellmap_table_kernel(const LevelItem* __restrict__ items,
@@ -828,7 +846,7 @@ hipError_t feat_single(const LevelItem& it, float clip, float eps, hipStream_t s
         constexpr int RW = 4;
         const int chunk = row_chunk<FEAT, CM>(RW);
         const int rows = (FEAT & PD_FEAT_HOG) && !CM ? std::max(it.hc - 1, 1) : it.hc;
-        features_rows_single_kernel<FEAT, CM, RW><<<dim3(ntx, ceil_div(rows, chunk)), RW * 64, 0, s>>>(it, clip, eps);
+        features_rows_single_kernel<FEAT, CM, RW><<<dim3(ntx, ceil_div(rows, chunk)), ROW_THREADS<FEAT, RW>, 0, s>>>(it, clip, eps);
     } else {
         const int n = ntx * feat_tiles_y(it.hc);
         features_single_kernel<FEAT, CM><<<ceil_div(n, FT_WAVES), FT_WAVES * 64, 0, s>>>(it, clip, eps);
@@ -848,7 +866,7 @@ hipError_t feat_table(const LevelItem* items, const Tile* tiles, int n_tiles, fl
 template <int FEAT>
 hipError_t feat_rows_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip, float eps,
                            hipStream_t s) {
-    features_rows_table_kernel<FEAT, FR_WAVES><<<dim3(n_tiles, FR_SPAN), FR_WAVES * 64, 0, s>>>(items, tiles, clip, eps);
+    features_rows_table_kernel<FEAT, FR_WAVES><<<dim3(n_tiles, FR_SPAN), ROW_THREADS<FEAT, FR_WAVES>, 0, s>>>(items, tiles, clip, eps);
     return hipGetLastError();
 }
 
