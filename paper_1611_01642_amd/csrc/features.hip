@@ -72,8 +72,8 @@ constexpr int VOTE_SLOTS = 2 * 3 * VOTE_BINS;
 
 // What the previous cell row leaves for the next stays in registers, and the
 // workgroup's LDS (lookup table, byte counters, vote accumulators: 76 KB)
-// leaves room for two workgroups per CU.  LBP alone has no accumulators (16 KB,
-// 7 workgroups by their registers): 128 frames of 1242x375 take 258 us, with
+// leaves room for two workgroups per CU.  LBP alone has no accumulators (17 KB,
+// 7 workgroups by their registers): 128 frames of 1242x375 take 242 us, with
 // room for two workgroups they took 413.
 template <int FEAT, int WAVES = FT_WAVES>
 struct FeatShared {
@@ -382,7 +382,10 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
     const int cx = CM ? cx0 - 1 + lane : cx0 + li;
     const int x0 = PD_CELL * min(max(cx, 0), wc - 1);  // lanes past the edges read valid pixels
     // a group past the level's last row chunk does nothing (empty row range)
-    const int cy_last = cy0 <= max(hc - 2, 0) || cy0 == 0 ? min(cy0 + ch, hc - 1) : cy0 - 1;
+    // (LBP alone leaves the row after the strip's to the next strip)
+    const int cy_last = cy0 <= max(hc - 2, 0) || cy0 == 0
+                            ? (DO_HOG || cy0 + ch >= hc - 1 ? min(cy0 + ch, hc - 1) : cy0 + ch - 1)
+                            : cy0 - 1;
     const int cy_start = (CM && cy0 > 0) ? cy0 - 1 : cy0;
     const bool own = !CM || (lane >= 1 && lane <= FT_BX_CM && cx < wc);
     const bool lbp_col = CM ? own : cx < wc && (li < group - 1 || cx == wc - 1);
@@ -567,8 +570,9 @@ __device__ __forceinline__ void features_strip(gptr<const uint8_t> __restrict__ 
 // A strip walks its cell rows in turn, 1.8 us per pixel row of its 64 cells (the
 // votes' LDS chains, with nothing else on the SIMD to cover them), so a launch
 // with few strips takes as long as one of them: 135 us for 8 block rows, for a
-// 320x240 frame as for a 1242x375 one.  In this form they take 20 and 32 us, a
-// level's cell map 25 us (from 180).  Here a workgroup's waves
+// 320x240 frame as for a 1242x375 one.  In this form they take 17 and 29 us, a
+// level's cell map 25 us (from 180); 22 and 32 with the LBP counted by the HOG's
+// waves.  Here a workgroup's waves
 // take one cell row each (lane groups: 64 / width rows each) and pass what the
 // strip keeps in registers from one row to the next through LDS, in the bytes
 // of the vote accumulators.  The sums are the strip's, term by term: the same

@@ -89,11 +89,11 @@ constexpr int FT_WAVES = 4;  // waves (independent strips) per workgroup
 // features of few strips: a wave per cell row
 constexpr int FR_WAVES = 4;           // cell rows (of 64 lanes) per workgroup
 constexpr int FR_SPAN = 8;            // workgroups per table entry
-// strip rows (64 cells of one cell row) of a launch at most: about 11 pyramids
-// of 1242x375, where the two forms meet (us here and in strips: 4 frames 56 and
-// 98, 8 frames 102 and 101, 10 frames 122 and 134, 12 frames 139 and 133, 16
-// frames 178 and 143; 2 frames of 1920x1080 116 and 133, 3 of them 162 and 135)
-constexpr int64_t FR_MAX_ROWS = 9000;
+// strip rows (64 cells of one cell row) of a launch at most: about 14 pyramids
+// of 1242x375, where the two forms meet (us here and in strips: 4 frames 50 and
+// 98, 8 frames 86 and 102, 12 frames 114 and 132, 14 frames 132 and 136, 16
+// frames 152 and 143; 3 frames of 1920x1080 136 and 134; 20 of 640x480 139 and 136)
+constexpr int64_t FR_MAX_ROWS = 11000;
 constexpr int SC_W = 64;  // window columns of a score tile
 // compaction: threads per workgroup, windows per thread, windows per workgroup
 constexpr int CP_THREADS = 256;
