@@ -765,17 +765,17 @@ __global__ void __launch_bounds__((ROW_THREADS<FEAT, RW>)) features_rows_single_
 
 // Table entry: item, ty = the first cell row, tx = strip, pad = lane-group
 // width; block y takes one of its FR_SPAN chunks of rows.
-template <int FEAT, int RW>
+template <int FEAT, bool CM, int RW>
 __global__ void __launch_bounds__((ROW_THREADS<FEAT, RW>)) features_rows_table_kernel(const LevelItem* __restrict__ items,
                                                                       const Tile* __restrict__ tiles, float clip,
                                                                       float eps) {
     __shared__ FeatShared<FEAT, RW> sm;
     const Tile tl = tiles[blockIdx.x];
     const LevelItem& it = items[tl.item];
-    const int cy0 = tl.ty + blockIdx.y * row_chunk<FEAT, false>(RW * (64 / tl.pad));
-    if (cy0 > 0 && cy0 >= ((FEAT & PD_FEAT_HOG) ? it.hc - 1 : it.hc)) return;
+    const int cy0 = tl.ty + blockIdx.y * row_chunk<FEAT, CM>(RW * (64 / tl.pad));
+    if (cy0 > 0 && cy0 >= ((FEAT & PD_FEAT_HOG) && !CM ? it.hc - 1 : it.hc)) return;
     init_lut<ROW_THREADS<FEAT, RW>>(sm.lut);
-    features_rows_wave<FEAT, false, RW>(it, cy0, tl.tx, tl.pad, clip, eps, sm);
+    features_rows_wave<FEAT, CM, RW>(it, cy0, tl.tx, tl.pad, clip, eps, sm);
 }
 
 __global__ void __launch_bounds__(FT_WAVES * 64) cellmap_table_kernel(const LevelItem* __restrict__ items,
@@ -867,16 +867,17 @@ hipError_t feat_table(const LevelItem* items, const Tile* tiles, int n_tiles, fl
     return hipGetLastError();
 }
 
-template <int FEAT>
+template <int FEAT, bool CM = false>
 hipError_t feat_rows_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip, float eps,
                            hipStream_t s) {
-    features_rows_table_kernel<FEAT, FR_WAVES><<<dim3(n_tiles, FR_SPAN), ROW_THREADS<FEAT, FR_WAVES>, 0, s>>>(items, tiles, clip, eps);
+    features_rows_table_kernel<FEAT, CM, FR_WAVES><<<dim3(n_tiles, FR_SPAN), ROW_THREADS<FEAT, FR_WAVES>, 0, s>>>(items, tiles, clip, eps);
     return hipGetLastError();
 }
 
 }  // namespace
 
-int feat_rows_chunk(int features, int width) {
+int feat_rows_chunk(int features, int width, bool cell_map) {
+    if (cell_map) return row_chunk<PD_FEAT_HOG | PD_FEAT_LBP, true>(FR_WAVES);
     const int R = FR_WAVES * (64 / width);
     return (features & PD_FEAT_HOG) ? row_chunk<PD_FEAT_HOG, false>(R) : row_chunk<PD_FEAT_LBP, false>(R);
 }
@@ -889,6 +890,12 @@ hipError_t launch_features_rows_table(const LevelItem* items, const Tile* tiles,
         case PD_FEAT_LBP: return feat_rows_table<PD_FEAT_LBP>(items, tiles, n_tiles, clip, eps, s);
         default: return feat_rows_table<PD_FEAT_HOG | PD_FEAT_LBP>(items, tiles, n_tiles, clip, eps, s);
     }
+}
+
+hipError_t launch_cellmap_rows_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip, float eps,
+                                     hipStream_t s) {
+    if (n_tiles <= 0) return hipSuccess;
+    return feat_rows_table<PD_FEAT_HOG | PD_FEAT_LBP, true>(items, tiles, n_tiles, clip, eps, s);
 }
 
 hipError_t launch_features_cellmap_single(const LevelItem& it, float clip, float eps, hipStream_t s) {

@@ -644,7 +644,7 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
     int64_t row_waves = 0;
     for (size_t k = 0; k < L.sizes.size(); k += 2)
         row_waves += (int64_t)feat_tiles_x(L.sizes[k] / PD_CELL) * (L.sizes[k + 1] / PD_CELL);
-    R.feat_rows = !L.prune && row_waves <= FR_MAX_ROWS;
+    R.feat_rows = row_waves <= (L.prune ? FR_MAX_ROWS_CM : FR_MAX_ROWS);
     if (!R.feat_rows) R.strip_rows = tu.feat_rows ? tu.feat_rows : strip_rows(L, features);
     const int rs_rows = resize_rows(L.n_rs);
     for (int f = 0; f < n_frames; ++f) {
@@ -681,7 +681,11 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
                     for (int tx = 0; tx < resize_tiles_x(it.w); ++tx) t_rs[nrs++] = Tile{q, y, tx, rs_rows};
             }
             const int fty = feat_tiles_y(it.hc, R.strip_rows);
-            if (L.prune) {
+            if (L.prune && R.feat_rows) {
+                const int step = FR_SPAN * feat_rows_chunk(features, 64, true);
+                for (int tx = 0; tx < feat_tiles_x_cm(it.wc); ++tx)
+                    for (int y = 0; y < it.hc; y += step) t_ft[nft++] = Tile{q, y, tx, 64};
+            } else if (L.prune) {
                 for (int ty = 0; ty < fty; ++ty)
                     for (int tx = 0; tx < feat_tiles_x_cm(it.wc); ++tx) t_ft[nft++] = Tile{q, ty, tx, 0};
             } else {
@@ -691,7 +695,7 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
                 if (R.feat_rows) {  // entries of FR_SPAN workgroups
                     for (int tx = 0; tx < full + narrow; ++tx) {
                         const int wd = tx < full ? 64 : width;
-                        const int step = FR_SPAN * feat_rows_chunk(features, wd);
+                        const int step = FR_SPAN * feat_rows_chunk(features, wd, false);
                         const int rows = (features & PD_FEAT_HOG) ? std::max(it.hc - 1, 1) : it.hc;
                         for (int y = 0; y < rows; y += step) t_ft[nft++] = Tile{q, y, tx, wd};
                     }
@@ -843,10 +847,10 @@ int enqueue_detect(const DetectRun& R, const DetectLayout& L, const Tuning& tu, 
     if ((rc = hip_status(launch_resize_table(R.items, R.t_rs, R.nrs, R.counters, R.n_zero, s), "resize"))) return rc;
     marks.mark(PD_STAGE_FEATURES, s);
     if (L.prune) {
-        if ((rc = hip_status(launch_features_cellmap_table(R.items, R.t_ft, R.nft, params->clip, params->eps, R.strip_rows,
-                                                                 tu.grid, s),
-                             "features + cell map")))
-            return rc;
+        const hipError_t e = R.feat_rows ? launch_cellmap_rows_table(R.items, R.t_ft, R.nft, params->clip, params->eps, s)
+                                         : launch_features_cellmap_table(R.items, R.t_ft, R.nft, params->clip,
+                                                                         params->eps, R.strip_rows, tu.grid, s);
+        if ((rc = hip_status(e, "features + cell map"))) return rc;
         marks.mark(PD_STAGE_SCORE, s);
         if ((rc = hip_status(launch_pruner_mfma(R.items, R.t_pr, R.npr, params->pruner, R.prpack, s), "pruner")))
             return rc;

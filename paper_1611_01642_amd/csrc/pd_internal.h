@@ -94,6 +94,9 @@ constexpr int FR_SPAN = 8;            // workgroups per table entry
 // 98, 8 frames 86 and 102, 12 frames 114 and 132, 14 frames 132 and 136, 16
 // frames 152 and 143; 3 frames of 1920x1080 136 and 134; 20 of 640x480 139 and 136)
 constexpr int64_t FR_MAX_ROWS = 11000;
+// with the pruner's cell map, where a workgroup of four rows stores two of them
+// (1 frame of 1242x375 37 and 123, 2 frames 66 and 123, 4 frames 126 and 126)
+constexpr int64_t FR_MAX_ROWS_CM = 3000;
 constexpr int SC_W = 64;  // window columns of a score tile
 // compaction: threads per workgroup, windows per thread, windows per workgroup
 constexpr int CP_THREADS = 256;
@@ -241,10 +244,12 @@ hipError_t launch_features_single(const LevelItem& it, int features, float clip,
 hipError_t launch_features_table(const LevelItem* items, const Tile* tiles, int n_tiles,
                                  int features, float clip, float eps, int rows, int grid, hipStream_t s);
 // The form for few strips (same bits): block rows per workgroup for strips of
-// `width` lanes, and its launch.
-int feat_rows_chunk(int features, int width);
+// `width` lanes (with the cell map: cell rows, full strips), and its launch.
+int feat_rows_chunk(int features, int width, bool cell_map);
 hipError_t launch_features_rows_table(const LevelItem* items, const Tile* tiles, int n_tiles, int features,
                                       float clip, float eps, hipStream_t s);
+hipError_t launch_cellmap_rows_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip, float eps,
+                                     hipStream_t s);
 // Fused HOG + LBP + pruner cell map (it.cmap), HOG|LBP only.
 hipError_t launch_features_cellmap_single(const LevelItem& it, float clip, float eps, hipStream_t s);
 hipError_t launch_features_cellmap_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip,

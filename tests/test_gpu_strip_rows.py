@@ -47,3 +47,25 @@ def test_chosen_rows(name, kw):
         res.append(([b.tobytes() for b in boxes], [c.tobytes() for c in counts]))
     assert sum(int(c["candidates"]) for c in counts) > 0
     assert all(r == res[0] for r in res[1:])
+
+
+@pytest.mark.parametrize("size", [(1242, 375), (64, 128), (520, 131), (513, 400)])
+def test_pruned_alone_and_in_a_batch(size):
+    """A pruned frame alone (its cell map by waves per cell row) and in a batch
+    long enough for strips: the same boxes."""
+    img = torch.from_numpy(pd_synth.frame(*size, 17)).to(DEV)
+    rest = [torch.from_numpy(f).to(DEV) for f in pd_synth.frame_batch([(1242, 375)] * 6, 5)]
+    wts = torch.from_numpy(pd_synth.svm_weights(1)).to(DEV)
+    pruner = torch.from_numpy(np.random.default_rng(3).normal(0, 0.05, pd.PRUNER_PARAMS).astype(np.float32)).to(DEV)
+    prm = pd.params(precision=pd.PREC_BF16, prune_keep=300, pruner=pruner)
+    out = []
+    for frames in ([img], rest + [img]):
+        det = pd.Detector(frames, wts, torch.zeros(1, device=DEV), prm, cap=512)
+        det.run(torch.full((len(frames),), -1.0e30, dtype=torch.float64, device=DEV))
+        torch.cuda.synchronize()
+        boxes, counts = det.results()
+        b = boxes[-1].copy()
+        b["frame"] = 0
+        out.append((b.tobytes(), counts[-1].tobytes()))
+    assert int(counts[-1]["candidates"]) > 0
+    assert out[0] == out[1]
