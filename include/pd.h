@@ -96,9 +96,11 @@ typedef struct pd_params {
     /* Tile and launch shapes of pd_detect (0 = default).  They change the
        work partition only, never a result; pd_autotune picks them.        */
     int32_t tune_feat_rows;  /* block rows per feature strip: 4..32
-                                (0: chosen by the strips' number)          */
+                                (0: chosen by the strips' number; batches of
+                                few strips take a form without them)       */
     int32_t tune_score_rows; /* PD_PREC_F32 window rows per scoring band:
-                                4, 8 or 16 (8)                             */
+                                4, 8 or 16 (8; batches of few windows take
+                                a form without bands)                      */
     int32_t tune_grid;       /* 0: default grids; n > 0: feature and
                                 scoring grids of at most n workgroups
                                 looping over the tiles                     */
@@ -534,7 +536,7 @@ int pd_graph_stage_ms(pd_graph* graph, double* ms);
  * A video stream of frames of one size that arrive one at a time in host
  * memory.  Each push copies the frame to the GPU (step 1), runs pd_detect's
  * kernels on it (steps 2-4 and NMS, as a graph captured at creation) and
- * copies the counts and boxes back (step 5), on three streams ordered by
+ * copies the counts and boxes back (step 5), on streams of its own ordered by
  * events, so the copies of one frame overlap the detection of its
  * neighbours.  Up to `depth` frames are in flight; results come back in push
  * order.  This object owns its buffers: pd_video_create allocates device
