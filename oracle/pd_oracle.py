@@ -22,7 +22,7 @@ the quantity is an integer, written for readability rather than speed:
                             to the hyper-plane exceeds a given threshold)
   * NMS                  -- Section 3 (refinement by non-maximum suppression)
 
-Readings of points the paper leaves open (each also listed in the design doc):
+Readings of points the paper leaves open:
   R1 level k is resized from level 0 with pixel-centre-aligned bilinear
      interpolation in Q8 fixed point, rounded half up; level sizes are
      floor(W0 * den^k / num^k) for the scale num/den; levels are kept while

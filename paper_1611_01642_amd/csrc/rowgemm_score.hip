@@ -45,6 +45,9 @@ struct RowShared {
     float ring[4][16][16];  // per wave: window-row slot x window column
 };
 
+// Staging takes channels in pairs: a thread loads both planes' values and writes
+// them as one word, half as many LDS writes as channel by channel (those were a
+// quarter of the kernel's LDS time: 224 -> 215 us for 64 frames of 1242x375).
 template <bool HOG>
 struct RowRegs {
     static constexpr int SR = HOG ? RG_HOG_SR : RG_LBP_SR;
@@ -52,22 +55,24 @@ struct RowRegs {
     // per plane row, HOG: SR BF16 values; LBP: the SR count bytes as 4-byte
     // words (columns 4 d .. 4 d + 3)
     static constexpr int UNITS = HOG ? SR : (SR + 3) / 4;
-    // LBP: elements in blocks of 8 channels x UNITS words x 8 (64 channel
-    // slots, those past the 59th empty), the channel fastest within a block
-    static constexpr int N = HOG ? (UNITS * NC + 255) / 256 : (UNITS * 64 + 255) / 256;
+    // elements: HOG, a pair's columns; LBP, blocks of 8 pairs x UNITS words (32
+    // pair slots, those past the 30th empty), the pair fastest within a block
+    static constexpr int N = HOG ? (UNITS * NC / 2 + 255) / 256 : (UNITS * 32 + 255) / 256;
     // HOG: BF16 bits; LBP: four raw counts (converted when stored)
-    std::conditional_t<HOG, uint16_t, uint32_t> v[N];
+    std::conditional_t<HOG, uint16_t, uint32_t> v[N][2];
 };
 
-// The per-thread offsets are taken once per tile: goff[q], the
-// element's byte offset in the planes without the row (raw buffer loads add
-// the row's byte offset as a scalar), and soff[q], its byte offset in the
-// staged row (LBP: that of the word's first column).  HOG elements past the
+// The per-thread offsets are taken once per tile: goff[q], the byte offset of
+// the element's first plane without the row (raw buffer loads add the row's byte
+// offset, and the second plane's, as a scalar), and soff[q], its byte offset in
+// the staged row (LBP: that of the word's first column).  HOG elements past the
 // last are clamped to it (same value, same place).  An LBP word is read from inside its
 // plane row: where columns 4 d .. 4 d + 3 reach past the row's end, from the
 // row's last four bytes, and shifted down by the difference (kept in the top
 // byte of soff), so that its columns inside the row get their counts; the
-// rest (past the level, feeding no stored window) get finite values.
+// rest (past the level, feeding no stored window) get finite values.  The last
+// LBP pair is channel 58 and an empty slot: channels 57 and 58 are loaded and
+// change places (bit 26), the empty slot's weight being zero.
 template <bool HOG>
 struct RowOffsets {
     uint32_t goff[RowRegs<HOG>::N], soff[RowRegs<HOG>::N];
@@ -77,31 +82,32 @@ template <bool HOG>
 __device__ __forceinline__ void row_offsets(RowOffsets<HOG>& o, int j0, int hcols, int hrows) {
     constexpr int U = RowRegs<HOG>::UNITS, NC = RowRegs<HOG>::NC;
     constexpr int C = HOG ? RG_HOG_C : RG_LBP_C;
+    static_assert(RG_HOG_C % 2 == 0 && RG_LBP_C % 2 == 0 && PD_HOG_BLOCK % 2 == 0, "pairs on word boundaries");
     const uint32_t plane = (uint32_t)hrows * (uint32_t)hcols;
 #pragma unroll
     for (int q = 0; q < RowRegs<HOG>::N; ++q) {
         if constexpr (HOG) {
-            const int e = min((int)threadIdx.x + 256 * q, U * NC - 1);
-            const int c = e / U, col = e - (e / U) * U;
+            const int e = min((int)threadIdx.x + 256 * q, U * NC / 2 - 1);
+            const int c = 2 * (e / U), col = e - (e / U) * U;
             o.goff[q] = ((uint32_t)c * plane + (uint32_t)min(j0 + col, hcols - 1)) * 2u;
             o.soff[q] = (uint32_t)(col * C + c) * 2u;
         } else {
-            // lanes by 8 channels x 8 words: a wave's staging writes fall in
-            // 32 banks (words 4 columns apart are 120 dwords apart, channels
-            // 2 bytes), its loads in 8 plane rows of 32 contiguous bytes.
-            // Slots past the last channel or element load channel 58's word
-            // and store nothing (bit 31 of soff).
+            // lanes by 8 pairs x 8 words: a wave's staging writes fall in 64
+            // banks (words 4 columns apart are 120 dwords apart, pairs one), its
+            // loads in 8 plane rows of 32 contiguous bytes.  Slots past the last
+            // pair or element load channel 57's word and store nothing (bit 31
+            // of soff).
             const int g = (int)threadIdx.x + 256 * q;
             const int cl = g & 7, rest = g >> 3;
             const int uu = rest % U, cb = rest / U;
-            const int cc = 8 * cb + cl;
-            const bool valid = cc < NC && cb < 8;
-            const int cs = min(cc, NC - 1), col4 = 4 * uu;
+            const int c = 2 * (8 * cb + cl);
+            const bool valid = c < NC && cb < 4;
+            const int cs = min(c, NC - 2), col4 = 4 * uu;
             // hcols >= 8 (a level holds at least one window)
             const int start = min(j0 + col4, hcols - 4);
             o.goff[q] = (uint32_t)cs * plane + (uint32_t)start;
-            o.soff[q] = (uint32_t)(col4 * C + cs) * 2u | (uint32_t)min(j0 + col4 - start, 3) << 24 |
-                        (valid ? 0u : 0x80000000u);
+            o.soff[q] = (uint32_t)(col4 * C + min(c, NC - 1)) * 2u | (uint32_t)min(j0 + col4 - start, 3) << 24 |
+                        (c == NC - 1 ? 1u << 26 : 0u) | (valid ? 0u : 0x80000000u);
         }
     }
 }
@@ -110,13 +116,16 @@ template <bool HOG>
 __device__ __forceinline__ void load_row_fast(RowRegs<HOG>& r, const RowOffsets<HOG>& o, __amdgpu_buffer_rsrc_t rsrc,
                                               int y, int hcols, int hrows) {
     const uint32_t roff = (uint32_t)min(y, hrows - 1) * (uint32_t)hcols * (HOG ? 2u : 1u);
+    const uint32_t plane = (uint32_t)hrows * (uint32_t)hcols * (HOG ? 2u : 1u);
 #pragma unroll
-    for (int q = 0; q < RowRegs<HOG>::N; ++q) {
-        // raw values: LBP counts are converted when stored, so that no
-        // instruction waits on these loads before the MFMAs they overlap
-        if (HOG) r.v[q] = __builtin_amdgcn_raw_buffer_load_b16(rsrc, o.goff[q], roff, 0);
-        else r.v[q] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, o.goff[q], roff, 0);
-    }
+    for (int q = 0; q < RowRegs<HOG>::N; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            // raw values: LBP counts are converted when stored, so that no
+            // instruction waits on these loads before the MFMAs they overlap
+            if (HOG) r.v[q][h] = __builtin_amdgcn_raw_buffer_load_b16(rsrc, o.goff[q], roff + h * plane, 0);
+            else r.v[q][h] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, o.goff[q], roff + h * plane, 0);
+        }
 }
 
 template <bool HOG>
@@ -125,22 +134,23 @@ __device__ __forceinline__ void store_row_fast(const RowRegs<HOG>& r, const RowO
 #pragma unroll
     for (int q = 0; q < RowRegs<HOG>::N; ++q) {
         if constexpr (HOG) {
-            *reinterpret_cast<uint16_t*>(d + o.soff[q]) = r.v[q];
+            *reinterpret_cast<uint32_t*>(d + o.soff[q]) = (uint32_t)r.v[q][0] | (uint32_t)r.v[q][1] << 16;
         } else {
             // LBP counts <= 64 are exact in BF16: the top half of their FP32
-            // value; byte k of the word is column 4 d + k (its channel's slot
+            // value; byte k of the word is column 4 d + k (its channels' slots
             // RG_LBP_C values further on), the last word's column 71 past the
             // staged row is skipped
             if (o.soff[q] & 0x80000000u) continue;
-            const uint32_t so = o.soff[q] & 0xffffffu;
-            const uint32_t w = r.v[q] >> (8u * ((o.soff[q] >> 24) & 3u));
+            const uint32_t so = o.soff[q] & 0xffffffu, shift = 8u * ((o.soff[q] >> 24) & 3u);
+            const uint32_t w0 = r.v[q][0] >> shift, w1 = r.v[q][1] >> shift;
+            const uint32_t halves = o.soff[q] & 1u << 26 ? 0x03020706u : 0x07060302u;
             const uint32_t col0 = so / (2u * RG_LBP_C);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const uint32_t b = (w >> (8 * k)) & 255u;
+                const uint32_t b0 = __float_as_uint((float)(w0 >> (8 * k) & 255u));
+                const uint32_t b1 = __float_as_uint((float)(w1 >> (8 * k) & 255u));
                 if (k < 3 || col0 + 3 < (uint32_t)RG_LBP_SR)
-                    *reinterpret_cast<uint16_t*>(d + so + k * 2 * RG_LBP_C) =
-                        (uint16_t)(__float_as_uint((float)b) >> 16);
+                    *reinterpret_cast<uint32_t*>(d + so + k * 2 * RG_LBP_C) = __builtin_amdgcn_perm(b1, b0, halves);
             }
         }
     }
