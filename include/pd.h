@@ -565,7 +565,8 @@ int pd_video_create(int w, int h, const pd_params* params, const float* weights,
  * copied before the call returns) with its detection threshold.  Returns
  * without waiting for the GPU.
  * Errors: PD_E_SIZE when `depth` frames are already in flight (pop first);
- * PD_E_ARG on a NULL frame or pitch < w.
+ * PD_E_ARG on a NULL frame or pitch < w; PD_E_HIP from the queueing (the frame
+ * is then not in flight, and what was queued of it has been waited for).
  */
 int pd_video_push(pd_video* v, const uint8_t* frame, int pitch, double threshold);
 

@@ -139,7 +139,7 @@ int pd_video_push(pd_video* v, const uint8_t* frame, int pitch, double threshold
     pd_video::Slot& s = v->slots[(v->head + v->n_busy) % v->depth];
     for (int y = 0; y < v->h; ++y) std::memcpy(s.h_frame + (size_t)y * v->pitch, frame + (size_t)y * pitch, v->w);
     *s.h_thr = threshold;
-    const hipStream_t compute = v->compute[v->pushed++ % 2];
+    const hipStream_t compute = v->compute[v->pushed % 2];
     int rc = hip_status(hipEventRecord(s.ev_start, v->up), "video record");
     if (!rc)
         rc = hip_status(hipMemcpyAsync(s.d_frame, s.h_frame, (size_t)v->pitch * v->h + sizeof(double),
@@ -156,7 +156,14 @@ int pd_video_push(pd_video* v, const uint8_t* frame, int pitch, double threshold
                                        hipMemcpyDeviceToHost, v->down),
                         "video download");
     if (!rc) rc = hip_status(hipEventRecord(s.ev_done, v->down), "video record");
-    if (rc) return rc;  // the slot stays free; streams hold whatever was enqueued
+    if (rc) {
+        // The slot stays free: its next push writes the pinned frame and may
+        // launch the graph on the other compute stream, so what this one has
+        // enqueued must be over by then.
+        for (hipStream_t q : {v->up, compute, v->down}) (void)hipStreamSynchronize(q);
+        return rc;
+    }
+    ++v->pushed;
     ++v->n_busy;
     return PD_OK;
 }
