@@ -623,6 +623,32 @@ int strip_rows(const DetectLayout& L, int features) {
     return best;
 }
 
+// The table entries of one level's features by waves per cell row, each of
+// FR_SPAN workgroups: emit(first cell row, strip, lane-group width).
+template <typename Emit>
+void feat_row_entries(int wc, int hc, bool cell_map, int features, Emit&& emit) {
+    const StripCols c = strip_cols(wc);
+    const int strips = cell_map ? feat_tiles_x_cm(wc) : c.full + c.narrow;
+    const int rows = !cell_map && (features & PD_FEAT_HOG) ? std::max(hc - 1, 1) : hc;
+    for (int tx = 0; tx < strips; ++tx) {
+        const int width = cell_map || tx < c.full ? 64 : c.width;
+        const int step = FR_SPAN * feat_rows_chunk(features, width, cell_map);
+        for (int y = 0; y < rows; y += step) emit(y, tx, width);
+    }
+}
+
+// Do the call's features take that form?  With few strips, unless tune_grid
+// asks for fewer workgroups than it launches (the strips loop over their tiles).
+bool few_strips(const DetectLayout& L, int features, int grid) {
+    int64_t strip_rows = 0, entries = 0;
+    for (size_t k = 0; k < L.sizes.size(); k += 2) {
+        const int wc = L.sizes[k] / PD_CELL, hc = L.sizes[k + 1] / PD_CELL;
+        strip_rows += (int64_t)feat_tiles_x(wc) * hc;
+        if (grid > 0) feat_row_entries(wc, hc, L.prune, features, [&](int, int, int) { ++entries; });
+    }
+    return strip_rows <= (L.prune ? FR_MAX_ROWS_CM : FR_MAX_ROWS) && (grid == 0 || entries * FR_SPAN <= grid);
+}
+
 // Builds the level, tile and NMS tables of one call in host memory `stage`
 // (L.table_bytes), laid out as they are uploaded to device memory `tbl`: the
 // start of the workspace `ws` for pd_detect, a graph's own buffer for a
@@ -641,10 +667,7 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
     Tile* t_cp = t_sc + L.n_sc;
     Tile* t_pr = t_cp + L.n_cp;
     int q = 0, nrs = 0, nft = 0, nsc = 0, ncp = 0, npr = 0;
-    int64_t row_waves = 0;
-    for (size_t k = 0; k < L.sizes.size(); k += 2)
-        row_waves += (int64_t)feat_tiles_x(L.sizes[k] / PD_CELL) * (L.sizes[k + 1] / PD_CELL);
-    R.feat_rows = row_waves <= (L.prune ? FR_MAX_ROWS_CM : FR_MAX_ROWS);
+    R.feat_rows = few_strips(L, features, tu.grid);
     if (!R.feat_rows) R.strip_rows = tu.feat_rows ? tu.feat_rows : strip_rows(L, features);
     const int rs_rows = resize_rows(L.n_rs);
     for (int f = 0; f < n_frames; ++f) {
@@ -681,29 +704,17 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
                     for (int tx = 0; tx < resize_tiles_x(it.w); ++tx) t_rs[nrs++] = Tile{q, y, tx, rs_rows};
             }
             const int fty = feat_tiles_y(it.hc, R.strip_rows);
-            if (L.prune && R.feat_rows) {
-                const int step = FR_SPAN * feat_rows_chunk(features, 64, true);
-                for (int tx = 0; tx < feat_tiles_x_cm(it.wc); ++tx)
-                    for (int y = 0; y < it.hc; y += step) t_ft[nft++] = Tile{q, y, tx, 64};
+            if (R.feat_rows) {
+                feat_row_entries(it.wc, it.hc, L.prune, features,
+                                 [&](int y, int tx, int width) { t_ft[nft++] = Tile{q, y, tx, width}; });
             } else if (L.prune) {
                 for (int ty = 0; ty < fty; ++ty)
                     for (int tx = 0; tx < feat_tiles_x_cm(it.wc); ++tx) t_ft[nft++] = Tile{q, ty, tx, 0};
             } else {
                 const StripCols c = strip_cols(it.wc);
-                const int full = c.full, width = c.width;
-                const bool narrow = c.narrow;
-                if (R.feat_rows) {  // entries of FR_SPAN workgroups
-                    for (int tx = 0; tx < full + narrow; ++tx) {
-                        const int wd = tx < full ? 64 : width;
-                        const int step = FR_SPAN * feat_rows_chunk(features, wd, false);
-                        const int rows = (features & PD_FEAT_HOG) ? std::max(it.hc - 1, 1) : it.hc;
-                        for (int y = 0; y < rows; y += step) t_ft[nft++] = Tile{q, y, tx, wd};
-                    }
-                } else {
-                    for (int ty = 0; ty < fty; ++ty)
-                        for (int tx = 0; tx < full; ++tx) t_ft[nft++] = Tile{q, ty, tx, 64};
-                    for (int ty = 0; narrow && ty < fty; ty += 64 / width) t_ft[nft++] = Tile{q, ty, full, width};
-                }
+                for (int ty = 0; ty < fty; ++ty)
+                    for (int tx = 0; tx < c.full; ++tx) t_ft[nft++] = Tile{q, ty, tx, 64};
+                for (int ty = 0; c.narrow && ty < fty; ty += 64 / c.width) t_ft[nft++] = Tile{q, ty, c.full, c.width};
             }
             if (L.prune) {
                 it.cmap16 = reinterpret_cast<uint16_t*>(data + L.cm_off[q]);
@@ -742,7 +753,7 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
         for (const Tile& t : by_item) t_ft[start[rows_of(t)]++] = t;
     }
     if (!L.bf16) {
-        R.s32_pairs = score32_wave_pairs((int64_t)L.n_sc * n_models);
+        R.s32_pairs = score32_wave_pairs((int64_t)L.n_sc * n_models, tu.grid);
         nsc = R.s32_pairs ? score32_wave_tiles(items, q, t_sc)
                           : score32_bands(items, q, tu.score_rows, tu.grid, t_sc, &R.xs, &R.s32_grid);
     }

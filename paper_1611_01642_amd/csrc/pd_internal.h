@@ -269,10 +269,10 @@ int64_t score32_packed_floats(int n_models);
 int score32_bands(const LevelItem* items, int n_items, int rows, int grid_cap, Tile* out, XcdLists* xs, int* grid);
 int64_t score32_band_capacity(int nx, int ny, int wc);
 // The form for few windows (same bits): its table, the row pairs per wave that
-// suit n_entries of it (0: too many, the band kernel), and its launch on the
+// suit n_entries of it under tune_grid's cap (0: the band kernel), and its launch on the
 // caller's own weights.
 int score32_wave_tiles(const LevelItem* items, int n_items, Tile* out);
-int score32_wave_pairs(int64_t n_entries);
+int score32_wave_pairs(int64_t n_entries, int grid_cap);
 // Threshold decisions taken as the FP32 scores are stored (one model, no
 // keep set): windows above their frame's threshold are appended to the
 // frame's candidate list as compaction appends them.  counters NULL: none.

@@ -814,9 +814,11 @@ int score32_wave_tiles(const LevelItem* items, int n_items, Tile* out) {
 // workgroup then has a CU of its own (one 1242x375 pyramid: 30 us, 44 with two
 // pairs), two up to about 32 such frames (4: 72 us, the band kernel 283; 16: 182
 // and 287; 32: 337 and 352), above that the band kernel (64: 680 and 550; 0).
-int score32_wave_pairs(int64_t n_entries) {
-    if (n_entries * SW_PAIRS <= 256) return 1;
-    return n_entries <= 700 ? 2 : 0;
+// The band kernel also where a cap on the grid (tune_grid) is below what this
+// form launches: it loops over its bands, this form does not.
+int score32_wave_pairs(int64_t n_entries, int grid_cap) {
+    const int pairs = n_entries * SW_PAIRS <= 256 ? 1 : n_entries <= 700 ? 2 : 0;
+    return pairs && grid_cap > 0 && n_entries * (SW_PAIRS / pairs) > grid_cap ? 0 : pairs;
 }
 
 // Table capacity for one level: the shortest bands over runs of 2 tiles, the
@@ -865,7 +867,7 @@ hipError_t launch_score_single(const LevelItem& it, const float* weights, const 
                                hipStream_t s) {
     if (it.nx <= 0 || it.ny <= 0 || n_models <= 0) return hipSuccess;
     const int n = ceil_div(it.ny, 2 * SW_PAIRS) * ceil_div(it.wc, SW_RUN * S32_TILE);
-    const int pairs = score32_wave_pairs((int64_t)n * n_models) == 1 ? 1 : 2;
+    const int pairs = score32_wave_pairs((int64_t)n * n_models, 0) == 1 ? 1 : 2;
     const dim3 g((unsigned)n, (unsigned)(SW_PAIRS / pairs), (unsigned)n_models);
     if (pairs == 1) score32_waves_single_kernel<1><<<g, SW_THREADS, 0, s>>>(it, weights, bias);
     else score32_waves_single_kernel<2><<<g, SW_THREADS, 0, s>>>(it, weights, bias);
