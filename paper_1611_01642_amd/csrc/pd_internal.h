@@ -255,8 +255,18 @@ hipError_t launch_features_cellmap_single(const LevelItem& it, float clip, float
 hipError_t launch_features_cellmap_table(const LevelItem* items, const Tile* tiles, int n_tiles, float clip,
                                          float eps, int rows, int grid, hipStream_t s);
 
-// FP32 scores of one image's windows (HOG and LBP), score32.hip.
+// FP32 scores of one image's windows (HOG and LBP), score.hip.
 hipError_t launch_score_single(const LevelItem& it, const float* w, const float* bias, int n_models, hipStream_t s);
+// by a wave per sub-tile (score32.hip) up to this many entries of its table over
+// all models, else by the vector-ALU kernel (us in waves and there: 473 entries,
+// 700x1400 cells, 430 and 456; 512, 270x480 and 8 models, 427 and 495; 528,
+// 540x960 and 2, 481 and 472; 792, the same and 3, 695 and 622; 992, 1000x2000,
+// 888 and 779; 2048 of 8 columns, 16 models, 915 and 821)
+constexpr int64_t SW_MAX_SINGLE = 512;
+constexpr bool score_single_by_waves(int64_t entries) { return entries <= SW_MAX_SINGLE; }
+int64_t score32_wave_entries(int ny, int wc);  // entries of one level
+hipError_t launch_score32_waves_single(const LevelItem& it, const float* w, const float* bias, int n_models,
+                                       hipStream_t s);
 // FP32 scoring on the matrix cores (score32.hip): bands of window rows over
 // runs of 16-column tiles, in 8 lists (one per XCD) taken through counters.
 struct XcdLists {

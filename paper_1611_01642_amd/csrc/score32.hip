@@ -810,6 +810,10 @@ int score32_wave_tiles(const LevelItem* items, int n_items, Tile* out) {
     return n;
 }
 
+int64_t score32_wave_entries(int ny, int wc) {
+    return (int64_t)ceil_div(ny, 2 * SW_PAIRS) * ceil_div(wc, SW_RUN * S32_TILE);
+}
+
 // Row pairs per wave for a launch of n_entries bands.  One pair while every
 // workgroup then has a CU of its own (one 1242x375 pyramid: 30 us, 44 with two
 // pairs), two up to about 32 such frames (4: 72 us, the band kernel 283; 16: 182
@@ -863,10 +867,9 @@ hipError_t launch_score32_waves_table(const LevelItem* items, const Tile* tiles,
     return hipGetLastError();
 }
 
-hipError_t launch_score_single(const LevelItem& it, const float* weights, const float* bias, int n_models,
-                               hipStream_t s) {
-    if (it.nx <= 0 || it.ny <= 0 || n_models <= 0) return hipSuccess;
-    const int n = ceil_div(it.ny, 2 * SW_PAIRS) * ceil_div(it.wc, SW_RUN * S32_TILE);
+hipError_t launch_score32_waves_single(const LevelItem& it, const float* weights, const float* bias, int n_models,
+                                       hipStream_t s) {
+    const int n = (int)score32_wave_entries(it.ny, it.wc);
     const int pairs = score32_wave_pairs((int64_t)n * n_models, 0) == 1 ? 1 : 2;
     const dim3 g((unsigned)n, (unsigned)(SW_PAIRS / pairs), (unsigned)n_models);
     if (pairs == 1) score32_waves_single_kernel<1><<<g, SW_THREADS, 0, s>>>(it, weights, bias);
