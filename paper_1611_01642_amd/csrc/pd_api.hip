@@ -753,7 +753,9 @@ void fill_tables(const pd_frame* frames, int n_frames, int n_models, int feature
         for (const Tile& t : by_item) t_ft[start[rows_of(t)]++] = t;
     }
     if (!L.bf16) {
-        R.s32_pairs = score32_wave_pairs((int64_t)L.n_sc * n_models, tu.grid);
+        int64_t units = 0;
+        for (int k = 0; k < q; ++k) units += score32_wave_units(items[k].ny, items[k].wc);
+        R.s32_pairs = score32_wave_pairs((int64_t)L.n_sc * n_models, units * n_models, tu.grid);
         nsc = R.s32_pairs ? score32_wave_tiles(items, q, t_sc)
                           : score32_bands(items, q, tu.score_rows, tu.grid, t_sc, &R.xs, &R.s32_grid);
     }

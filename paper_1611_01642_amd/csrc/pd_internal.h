@@ -264,7 +264,6 @@ hipError_t launch_score_single(const LevelItem& it, const float* w, const float*
 // 888 and 779; 2048 of 8 columns, 16 models, 915 and 821)
 constexpr int64_t SW_MAX_SINGLE = 512;
 constexpr bool score_single_by_waves(int64_t entries) { return entries <= SW_MAX_SINGLE; }
-int64_t score32_wave_entries(int ny, int wc);  // entries of one level
 hipError_t launch_score32_waves_single(const LevelItem& it, const float* w, const float* bias, int n_models,
                                        hipStream_t s);
 // FP32 scoring on the matrix cores (score32.hip): bands of window rows over
@@ -278,11 +277,37 @@ int64_t score32_packed_floats(int n_models);
 // the sum of score32_band_capacity over the items); returns its entry count.
 int score32_bands(const LevelItem* items, int n_items, int rows, int grid_cap, Tile* out, XcdLists* xs, int* grid);
 int64_t score32_band_capacity(int nx, int ny, int wc);
-// The form for few windows (same bits): its table, the row pairs per wave that
-// suit n_entries of it under tune_grid's cap (0: the band kernel), and its launch on the
-// caller's own weights.
+// The form for few windows (same bits): a wave per sub-tile of 16 feature columns
+// and one or two row pairs; a table entry is SW_PAIRS row pairs x SW_RUN tiles of
+// a level.
+constexpr int SW_PAIRS = 8;
+constexpr int SW_RUN = 2;
+constexpr int SW_MAX_ENTRIES = 700;
+// Row pairs per wave for a call with `entries` of them and `units` pairs of a
+// sub-tile and a row pair, both over all models (0: the band kernel).
+// One pair while every workgroup then has a CU of its own (one 1242x375 pyramid:
+// 30 us, 44 with two pairs).  Two while the launch is shorter than the band
+// kernel's longest band: a workgroup takes a slot of the chip whether its entry
+// is full (64 units) or holds one narrow level, the bands of such levels are
+// short, so the line falls with the units per entry.  us of a call by waves and
+// by bands: 16 frames of 1242x375 (336 entries, 32 units each) 370 and 476, 32
+// frames 662 and 711, 40 frames 822 and 817; 24 of 640x480 (576, 23) 511 and 527,
+// 32 (768) 652 and 605; 40 of 320x240 (280, 11) 182 and 190, 60 (420) 253 and
+// 233; 32 of 200x213 (192, 7) 110 and 123, 48 (288) 149 and 143, 110 (660) 323
+// and 255; 8 models, 4 frames of 1242x375 (672, 32) 510 and 622, 8 of 200x213
+// (384, 7) 157 and 146.
+// The band kernel also where a cap on the grid (tune_grid) is below what this
+// form launches: it loops over its bands, this form does not.
+constexpr int score32_wave_pairs(int64_t entries, int64_t units, int grid_cap) {
+    const int pairs = entries * SW_PAIRS <= 256 ? 1
+                      : entries <= 250 || (entries <= SW_MAX_ENTRIES && entries * entries <= 27 * units) ? 2 : 0;
+    return pairs && grid_cap > 0 && entries * (SW_PAIRS / pairs) > grid_cap ? 0 : pairs;
+}
+// Entries and units of one level; the table, and its launch on the caller's own
+// weights.
+int64_t score32_wave_entries(int ny, int wc);
+int64_t score32_wave_units(int ny, int wc);
 int score32_wave_tiles(const LevelItem* items, int n_items, Tile* out);
-int score32_wave_pairs(int64_t n_entries, int grid_cap);
 // Threshold decisions taken as the FP32 scores are stored (one model, no
 // keep set): windows above their frame's threshold are appended to the
 // frame's candidate list as compaction appends them.  counters NULL: none.

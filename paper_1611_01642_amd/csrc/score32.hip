@@ -388,8 +388,6 @@ score32_kernel(const LevelItem* __restrict__ items, const Tile* __restrict__ ban
 // the lead sub-tile (left of the entry, only its carry is wanted) and the 8
 // sub-tiles of the two tiles.  The model is packed into LDS straight from the
 // caller's weights, so no packing launch precedes this one.
-constexpr int SW_PAIRS = 8;             // row pairs per table entry
-constexpr int SW_RUN = 2;               // tiles per table entry
 constexpr int SW_SUBS = SW_RUN * S32_SUBS;
 constexpr int SW_THREADS = 64 * (SW_SUBS + 1);  // a wave per sub-tile, and one for the lead sub-tile
 constexpr int SW_WG_HOG = PD_HOG_DIM / 4;  // 16-byte pieces of a model's weights
@@ -814,16 +812,7 @@ int64_t score32_wave_entries(int ny, int wc) {
     return (int64_t)ceil_div(ny, 2 * SW_PAIRS) * ceil_div(wc, SW_RUN * S32_TILE);
 }
 
-// Row pairs per wave for a launch of n_entries bands.  One pair while every
-// workgroup then has a CU of its own (one 1242x375 pyramid: 30 us, 44 with two
-// pairs), two up to about 32 such frames (4: 72 us, the band kernel 283; 16: 182
-// and 287; 32: 337 and 352), above that the band kernel (64: 680 and 550; 0).
-// The band kernel also where a cap on the grid (tune_grid) is below what this
-// form launches: it loops over its bands, this form does not.
-int score32_wave_pairs(int64_t n_entries, int grid_cap) {
-    const int pairs = n_entries * SW_PAIRS <= 256 ? 1 : n_entries <= 700 ? 2 : 0;
-    return pairs && grid_cap > 0 && n_entries * (SW_PAIRS / pairs) > grid_cap ? 0 : pairs;
-}
+int64_t score32_wave_units(int ny, int wc) { return (int64_t)ceil_div(ny, 2) * ceil_div(wc, S32_SUB); }
 
 // Table capacity for one level: the shortest bands over runs of 2 tiles, the
 // finest the builder makes.
@@ -870,7 +859,7 @@ hipError_t launch_score32_waves_table(const LevelItem* items, const Tile* tiles,
 hipError_t launch_score32_waves_single(const LevelItem& it, const float* weights, const float* bias, int n_models,
                                        hipStream_t s) {
     const int n = (int)score32_wave_entries(it.ny, it.wc);
-    const int pairs = score32_wave_pairs((int64_t)n * n_models, 0) == 1 ? 1 : 2;
+    const int pairs = (int64_t)n * n_models * SW_PAIRS <= 256 ? 1 : 2;
     const dim3 g((unsigned)n, (unsigned)(SW_PAIRS / pairs), (unsigned)n_models);
     if (pairs == 1) score32_waves_single_kernel<1><<<g, SW_THREADS, 0, s>>>(it, weights, bias);
     else score32_waves_single_kernel<2><<<g, SW_THREADS, 0, s>>>(it, weights, bias);

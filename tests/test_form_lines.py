@@ -22,3 +22,20 @@ def test_scores_of_one_image(tmp_path):
                 473: (430, 456), 512: (427, 495), 792: (695, 622), 992: (888, 779), 1056: (909, 787),
                 2048: (2017, 1503), 2112: (1763, 1506)}
     holds(tmp_path, *(f"{'' if waves < valu else '!'}score_single_by_waves({n})" for n, (waves, valu) in measured.items()))
+
+
+def test_fp32_scores_of_a_batch(tmp_path):
+    # (entries, units) over all models: us of a call with waves of two row pairs, us with bands
+    measured = {(96, 656): (70, 109), (192, 1312): (110, 123), (384, 2624): (192, 165), (660, 4510): (323, 255),
+                (500, 1500): (170, 150), (750, 2250): (274, 216), (140, 1540): (123, 149), (420, 4620): (253, 233),
+                (560, 6160): (322, 275), (192, 4480): (208, 383), (384, 8960): (361, 446), (576, 13440): (511, 527),
+                (960, 22400): (803, 676), (336, 10640): (370, 476), (672, 21280): (662, 711), (672, 29274): (930, 1012),
+                # 8 models
+                (768, 5248): (244, 198), (1536, 10496): (423, 288), (1536, 35840): (958, 807)}
+    holds(tmp_path, *(f"score32_wave_pairs({n}, {u}, 0) == {2 if waves < bands else 0}"
+                      for (n, u), (waves, bands) in measured.items()),
+          # one row pair: 21 entries 30 us, 44 with two; 32 entries 72 and 85
+          "score32_wave_pairs(21, 665, 0) == 1", "score32_wave_pairs(32, 1280, 0) == 1",
+          # the cap: 168 entries of 4 workgroups
+          "score32_wave_pairs(168, 5320, 672) == 2", "score32_wave_pairs(168, 5320, 671) == 0",
+          "score32_wave_pairs(10, 300, 80) == 1", "score32_wave_pairs(10, 300, 79) == 0")
