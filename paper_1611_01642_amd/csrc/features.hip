@@ -846,7 +846,7 @@ __global__ void __launch_bounds__(256) lbp_codes_kernel(const uint8_t* __restric
 template <int FEAT, bool CM>
 hipError_t feat_single(const LevelItem& it, float clip, float eps, hipStream_t s) {
     const int ntx = CM ? feat_tiles_x_cm(it.wc) : feat_tiles_x(it.wc);
-    if ((int64_t)ntx * it.hc <= FR_MAX_ROWS) {
+    if ((int64_t)ntx * it.hc <= (CM ? FR_MAX_ROWS_CM_ONE : FR_MAX_ROWS)) {
         constexpr int RW = 4;
         const int chunk = row_chunk<FEAT, CM>(RW);
         const int rows = (FEAT & PD_FEAT_HOG) && !CM ? std::max(it.hc - 1, 1) : it.hc;

@@ -97,6 +97,10 @@ constexpr int64_t FR_MAX_ROWS = 11000;
 // with the pruner's cell map, where a workgroup of four rows stores two of them
 // (1 frame of 1242x375 37 and 123, 2 frames 66 and 123, 4 frames 126 and 126)
 constexpr int64_t FR_MAX_ROWS_CM = 3000;
+// and of one image with the cell map (strips of 8 block rows: 184 us up to 8000
+// strip rows; 5120x2880, 3960 strip rows, 136; 5120x3600, 4950, 168; 6144x3600,
+// 5850, 200; 7680x4320, 8640, 288 and 235 in strips)
+constexpr int64_t FR_MAX_ROWS_CM_ONE = 5400;
 constexpr int SC_W = 64;  // window columns of a score tile
 // compaction: threads per workgroup, windows per thread, windows per workgroup
 constexpr int CP_THREADS = 256;

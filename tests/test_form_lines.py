@@ -39,3 +39,12 @@ def test_fp32_scores_of_a_batch(tmp_path):
           # the cap: 168 entries of 4 workgroups
           "score32_wave_pairs(168, 5320, 672) == 2", "score32_wave_pairs(168, 5320, 671) == 0",
           "score32_wave_pairs(10, 300, 80) == 1", "score32_wave_pairs(10, 300, 79) == 0")
+
+
+def test_features_of_one_image(tmp_path):
+    # strip rows: us by a wave per cell row, us in strips
+    cell_map = {2160: (84, 185), 3456: (120, 184), 3960: (136, 184), 4400: (151, 184), 4950: (168, 184), 5850: (200, 184),
+                6144: (199, 184), 6656: (218, 185), 8640: (288, 235), 9775: (329, 247), 10240: (333, 237)}
+    plain = {3960: (56, 141), 6656: (88, 141), 8640: (114, 183), 10240: (109, 185)}
+    holds(tmp_path, *(f"{n} {'<=' if rows < strips else '>'} FR_MAX_ROWS_CM_ONE" for n, (rows, strips) in cell_map.items()),
+          *(f"{n} {'<=' if rows < strips else '>'} FR_MAX_ROWS" for n, (rows, strips) in plain.items()))
