@@ -594,7 +594,9 @@ int pd_video_destroy(pd_video* v);
  * compared.  Fields tried one at a time: feature strip rows {4, 6, 8, 10,
  * 12, 14, 16}, FP32 scoring rows {4, 8, 16}, grid cap {0, 256, 512, 1024,
  * 2048};
- * starting from params' own values.  Writes params with the fastest fields to
+ * starting from params' own values (strip rows of 0: the rows the call takes
+ * by itself, or 8 where it takes no strips).  Candidates that launch the same
+ * as the current choice are not timed.  Writes params with the fastest fields to
  * *best (host) and its device time per call in ms to *best_ms (host, may be
  * NULL).  Blocks until the timing runs finished; leaves boxes and counts of
  * the last run.  The workspace size does not depend on the tuning fields;

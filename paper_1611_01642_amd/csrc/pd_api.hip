@@ -2,6 +2,7 @@
 // launch sequence of the detection pipeline.  No allocation happens here:
 // every device buffer comes from the caller.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -1526,13 +1527,29 @@ int pd_autotune(const pd_frame* frames, int n_frames, const float* weights, cons
                 void* stream) {
     if (!best) return fail(PD_E_ARG, "best is NULL");
     if (iters < 1 || iters > 1000) return fail(PD_E_ARG, "iters outside [1, 1000]");
-    {
-        DetectLayout L;
-        if (int rc = validate_detect(frames, n_frames, weights, bias, n_models, params, thresholds, workspace,
-                                     workspace_bytes, boxes, cap, counts, L))
-            return rc;
-    }
+    DetectLayout L;
+    if (int rc = validate_detect(frames, n_frames, weights, bias, n_models, params, thresholds, workspace,
+                                 workspace_bytes, boxes, cap, counts, L))
+        return rc;
     hipStream_t s = (hipStream_t)stream;
+    // What the tuning fields make of this call's launches: candidates that
+    // change none of it are the same kernels, and are not timed (a call of few
+    // strips or few windows takes no notice of the strips' or bands' rows).
+    std::vector<uint8_t> tables((size_t)L.table_bytes);
+    auto plan = [&](const pd_params& p) {
+        DetectRun R;
+        uint8_t* const ws = static_cast<uint8_t*>(workspace);
+        fill_tables(frames, n_frames, n_models, p.features, tuning_of(&p), L, ws, ws, tables.data(), R);
+        return R;
+    };
+    auto shape = [&](const pd_params& p) {
+        const DetectRun R = plan(p);
+        const Tuning t = tuning_of(&p);
+        auto capped = [&](int n) { return t.grid > 0 ? std::min(n, t.grid) : n; };
+        return std::array<int, 6>{R.feat_rows ? 0 : R.strip_rows, R.feat_rows ? R.nft : capped(ceil_div(R.nft, FT_WAVES)),
+                                  R.s32_pairs, L.bf16 || R.s32_pairs ? 0 : t.score_rows, R.s32_grid,
+                                  L.bf16 ? capped(R.nsc) : R.nsc};
+    };
     const bool prof = g_prof.on;
     g_prof.on = false;  // tuning calls stay out of the stage profile
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1581,9 +1598,13 @@ int pd_autotune(const pd_frame* frames, int n_frames, const float* weights, cons
     };
     pd_params cur = *params;
     const Tuning t0 = tuning_of(params);
-    cur.tune_feat_rows = t0.feat_rows ? t0.feat_rows : FT_CH;
+    if (!cur.tune_feat_rows) {  // the rows the call takes by itself
+        const DetectRun R = plan(cur);
+        cur.tune_feat_rows = R.feat_rows ? FT_CH : R.strip_rows;
+    }
     cur.tune_score_rows = t0.score_rows;
     float cur_ms = 0.0f;
+    bool timed = false;
     // one knob at a time (the stages they shape are independent)
     const int feat_rows[] = {4, 6, 8, 10, 12, 14, 16};
     const int score_rows[] = {4, 8, 16};
@@ -1598,15 +1619,20 @@ int pd_autotune(const pd_frame* frames, int n_frames, const float* weights, cons
             const int now = knob == 0 ? cur.tune_feat_rows : knob == 1 ? cur.tune_score_rows : cur.tune_grid;
             if (vals[v] == now) continue;
             field = vals[v];
+            if (shape(c) == shape(cur)) continue;
             float ms_cur = 0.0f, ms = 0.0f;
             rc = time_pair(cur, c, &ms_cur, &ms);
-            if (!rc) cur_ms = ms_cur;
+            if (!rc) {
+                cur_ms = ms_cur;
+                timed = true;
+            }
             if (!rc && ms < ms_cur) {
                 cur = c;
                 cur_ms = ms;
             }
         }
     }
+    if (!rc && !timed) rc = time_shape(cur, &cur_ms);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     g_prof.on = prof;
