@@ -10,8 +10,9 @@
 // tables reach the device as kernel arguments (no staging buffer, no copy),
 // so the call allocates no device or pinned host memory.  Every call on a GPU
 // shares that GPU's array: overlapping calls on one GPU race.  The candidate
-// and near counters are cleared by the first kernel of every call, and every
-// other byte a call reads is written earlier in that call.
+// and near counters are cleared in every call by its resize launch, before any
+// kernel counts, and every other byte a call reads is written earlier in that
+// call.
 #include <algorithm>
 #include <cstring>
 #include <mutex>

@@ -816,6 +816,7 @@ int64_t score32_wave_units(int ny, int wc) { return (int64_t)ceil_div(ny, 2) * c
 
 // Table capacity for one level: the shortest bands over runs of 2 tiles, the
 // finest the builder makes.
+static_assert(SW_PAIRS == s32_pairs(4) && SW_RUN == 2, "a level's capacity is its number of wave entries");
 int64_t score32_band_capacity(int nx, int ny, int wc) {
     if (nx <= 0 || ny <= 0) return 0;
     return (int64_t)ceil_div(ny, 2 * s32_pairs(4)) * ceil_div(ceil_div(wc, S32_TILE), 2);
