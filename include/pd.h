@@ -406,8 +406,8 @@ int pd_detect(const pd_frame* frames, int n_frames, const float* weights,
  * on one stream are safe: each clears its counters before use.
  * Errors: those of pd_detect; PD_E_WORKSPACE, before any GPU work, when the
  * batch needs more than PD_NOALLOC_SCRATCH_BYTES of workspace
- * (pd_detect_workspace_bytes: a 1242x375 frame needs about 10 MiB, a
- * 1920x1080 frame about 50 MiB).
+ * (pd_detect_workspace_bytes: a 1242x375 frame needs about 9.4 MiB, a
+ * 1920x1080 frame about 48 MiB).
  */
 #define PD_NOALLOC_SCRATCH_BYTES (64ll << 20)
 int pd_detect_noalloc(const pd_frame* frames, int n_frames, const float* weights,

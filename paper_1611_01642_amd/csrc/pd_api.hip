@@ -334,11 +334,11 @@ bool plan_detect(const pd_frame* frames, int n_frames, const pd_params* p, int n
             frame_windows += (int64_t)it.nx * it.ny;
             L.sizes.push_back(wh[k][0]);
             L.sizes.push_back(wh[k][1]);
-            // (level 0 is read from the frame itself, whatever its alignment:
-            // a copy of rows that are not 8-byte aligned took 29 us for 256
-            // frames of 1242x375)
+            // (level 0 is read from the frame itself, whatever its alignment,
+            // and has no place here: a copy of rows that are not 8-byte aligned
+            // took 29 us for 256 frames of 1242x375)
             L.pyr_off.push_back(data);
-            data = align_up(data + (int64_t)align_up(it.w, 16) * it.h, kAlign);
+            if (k > 0) data = align_up(data + (int64_t)align_up(it.w, 16) * it.h, kAlign);
             L.hog_off.push_back(data);
             data = align_up(data + (int64_t)PD_HOG_BLOCK * it.hb * it.wb * (L.bf16 ? 2 : 4), kAlign);
             L.lbp_off.push_back(data);
